@@ -1,0 +1,40 @@
+"""GPU check that a beam's streams do not depend on how many share a call: S
+streams, from fewer than the 8 blockIdx classes to a ragged number of them,
+equal the same streams inside a call of 24, bit for bit (that call is a whole
+multiple of the classes; its decode is checked against the oracle elsewhere)."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_14991_amd as F
+from workloads import tiny_random_lm, tiny_random_phrases
+
+pytestmark = pytest.mark.gpu
+
+
+def _decode(glm, gtr, x, S, B, k, V, flags):
+    H = S * B
+    ls = torch.full((1, H), V, dtype=torch.int32, device="cuda")
+    bs = torch.zeros((H,), dtype=torch.int32, device="cuda")
+    sc = torch.from_numpy(np.tile(np.array([0.0] + [-np.inf] * (B - 1)), S)).to("cuda")
+    out = F.run_lms([glm], [0.5], gtr, x.contiguous(), S, B, k, 0.5, 0, F.FUSION_BLANK_COMPETE, ls, bs, sc,
+                    recombine=flags)
+    torch.cuda.synchronize()
+    assert F.fusion_device_status() == 0
+    return [t.cpu().reshape(-1, S, B) for t in (out["tokens"], out["parents"], ls, bs, sc)]
+
+
+@pytest.mark.parametrize("V,B", [(200, 3), (700, 4), (1500, 8)])
+@pytest.mark.parametrize("recombine", [False, True])
+def test_streams_are_independent_of_the_launch(V, B, recombine):
+    rng = np.random.default_rng(V + B)
+    k = 4
+    glm = F.ngram_load_arrays(tiny_random_lm(rng, V, 3, n_sent=2000))
+    gtr = F.boost_build_phrases(V, 0, tiny_random_phrases(rng, V, n=30, max_len=4, alphabet=30))
+    x = torch.from_numpy((rng.standard_normal((9, 24 * B, V)) * 2).astype(np.float32)).to("cuda")
+    whole = _decode(glm, gtr, x, 24, B, k, V, recombine)
+    for S in (1, 2, 7, 9, 23):
+        part = _decode(glm, gtr, x[:, :S * B], S, B, k, V, recombine)
+        for a, b in zip(part, whole):
+            assert torch.equal(a, b[:, :S]), (V, B, S)
