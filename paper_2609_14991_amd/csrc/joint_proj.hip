@@ -9,18 +9,19 @@
 //
 // Tiling for gfx950: a workgroup of WM x WN waves computes a (16 TM WM) x
 // (16 TN WN) output tile, each wave (16 TM) x (16 TN) as a TM x TN grid of
-// v_mfma_f32_16x16x32_bf16 tiles (4 TM TN fp32 accumulators per lane); the
-// larger the wave's tile, the fewer LDS bytes each multiply-accumulate reads.
-// K advances in stages of BK, double-buffered in LDS (rows padded by 16
-// bytes); every lane fetches its 16-byte strips of A and W two stages ahead
-// into one of two register sets, so a load has two stages of MFMAs to arrive
-// in.  The logits leave with streaming (non-temporal) stores.  Tiles are
-// assigned per XCD (see the kernel) so that each XCD's L2 serves a row band of
-// A to the column tiles of its half and keeps half of W.
+// v_mfma_f32_16x16x32_bf16 tiles.  K advances in stages of 64, NB of them in
+// LDS; the operands go straight from global memory to LDS (16 bytes a lane, no
+// registers, no LDS store instructions), NB - 1 stages ahead, with one barrier
+// a stage that waits for the oldest stage's loads only.  A stage's rows are 128
+// bytes, all LDS banks, so a fragment read (16 rows, one 16-byte chunk of each)
+// would hit the same banks in every row: chunk c of row r is kept in slot
+// c ^ (r % 8), which the loading lane arranges by the global chunk it picks.
+// SQ_LDS_BANK_CONFLICT reads 0 (rows padded by 16 bytes: 47 % of the LDS's
+// active cycles).  The MFMA operands are swapped (W rows as the tile's rows),
+// so a lane ends with 4 consecutive columns of one output row.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <type_traits>
 
 #include "fusion_internal.h"
 
@@ -31,30 +32,43 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
+constexpr int kBK = 64;                       // K per stage
+constexpr uint32_t kOutside = 0x80000000u;    // an offset past every descriptor (operands are under 2 GiB)
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);
 }
+// 16 bytes per lane straight into LDS (lane l lands at lds + 16 l)
+__device__ __forceinline__ void load_lds(__amdgpu_buffer_rsrc_t r, unsigned char *lds, uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds, 16, voff, soff, 0, 0);
+}
+// Barrier that also waits for this wave's LDS reads and for all but its N newest
+// vector-memory operations (the loads into LDS count there, in order)
+template <int N>
+__device__ __forceinline__ void wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
 
-// kWM x kWN waves, each a (16 kTM) x (16 kTN) output tile; K stages of kBK
-template <int kWM, int kWN, int kBK, int kTM, int kTN>
-__global__ void __launch_bounds__(64 * kWM * kWN) joint_proj_kernel(const uint16_t *__restrict__ A,
-                                                                     const uint16_t *__restrict__ W,
-                                                                     const float *__restrict__ bias, int M, int N,
-                                                                     int K, int n_col_tiles, int xcd_map, int vec_out,
-                                                                     float *__restrict__ out) {
+// kWM x kWN waves, each a (16 kTM) x (16 kTN) output tile; kNB stages in LDS;
+// kAux: cache policy of the output stores (see joint_project)
+template <int kWM, int kWN, int kTM, int kTN, int kNB, int kAux>
+__global__ void __launch_bounds__(64 * kWM * kWN, 2) joint_proj_kernel(const uint16_t *__restrict__ A,
+                                                                        const uint16_t *__restrict__ W,
+                                                                        const float *__restrict__ bias, int M, int N,
+                                                                        int K, int n_col_tiles, int xcd_map,
+                                                                        float *__restrict__ out) {
   constexpr int kRM = 16 * kTM, kRN = 16 * kTN;  // rows and columns of a wave's tile
-  constexpr int kBM = kRM * kWM, kBN = kRN * kWN;
-  constexpr int kLd = kBK + 8;  // bf16 per LDS row (16-byte pad)
-  constexpr int kThreads = 64 * kWM * kWN;
-  constexpr int kStripsA = kBM * kBK / 8 / kThreads;  // 16-byte strips per thread and stage
-  constexpr int kStripsW = kBN * kBK / 8 / kThreads;
-  constexpr int kChunks = kBK / 8;                     // strips per row
-  // one LDS block: the double-buffered operand stages, reused by the epilogue
-  __shared__ __align__(16) uint16_t smem[2 * (kBM + kBN) * kLd];
-  uint16_t(*sA)[kBM * kLd] = reinterpret_cast<uint16_t(*)[kBM * kLd]>(smem);
-  uint16_t(*sW)[kBN * kLd] = reinterpret_cast<uint16_t(*)[kBN * kLd]>(smem + 2 * kBM * kLd);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  constexpr int kBM = kRM * kWM, kBN = kRN * kWN, kWaves = kWM * kWN;
+  constexpr int kChunks = kBK / 8;               // 16-byte chunks per row and stage
+  constexpr int kRowsPer = 64 / kChunks;         // rows one wave-wide load brings (1 KiB)
+  constexpr int kLA = kBM / kRowsPer / kWaves, kLW = kBN / kRowsPer / kWaves, kL = kLA + kLW;  // loads per wave
+  static_assert(kLA * kRowsPer * kWaves == kBM && kLW * kRowsPer * kWaves == kBN, "whole loads per wave");
+  constexpr int kStage = (kBM + kBN) * kBK * 2;  // bytes of a stage
+  constexpr int kSeg = kRN < 64 ? kRN : 64, kLanes = kSeg / 4, kRowsI = 64 / kLanes;  // epilogue: see there
+  static_assert(kNB * kStage >= kWaves * 16 * kSeg * 4, "LDS too small for the epilogue");
+  __shared__ __align__(1024) unsigned char smem[kNB * kStage];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // tile of this workgroup.  With xcd_map (row tiles a multiple of 4, column
   // tiles even) workgroup w runs on XCD w % 8 under the hardware's round-robin,
   // and XCD x takes the row tiles = x % 4 (mod 4) against column half x / 4: a
@@ -73,37 +87,25 @@ __global__ void __launch_bounds__(64 * kWM * kWN) joint_proj_kernel(const uint16
   const int bn = tc * kBN, bm = tr * kBM;
   const int wm = (wave / kWN) * kRM, wn = (wave % kWN) * kRN;
 
-  // reads past a row range or past K return zeros (buffer range check)
+  // Load j of a stage brings rows (j * kWaves + wave) * kRowsPer .. of A (j < kLA)
+  // or W to consecutive LDS: lane l lands 16 l bytes in, i.e. row l / 8, slot
+  // l % 8, and fetches the chunk which that slot holds.  Rows past the operand
+  // and, in a ragged last stage, chunks past K read as zeros (range check).
   const __amdgpu_buffer_rsrc_t ra = rsrc(A, (uint32_t)((int64_t)M * K * 2));
   const __amdgpu_buffer_rsrc_t rw = rsrc(W, (uint32_t)((int64_t)N * K * 2));
-  // strip c = tid + kThreads * i of a stage: row c / kChunks, K offset (c % kChunks) * 8
-  auto fetch = [&](int k0, i32x4 (&ga)[kStripsA], i32x4 (&gw)[kStripsW]) {
+  const int lr = lane / kChunks, lc = (lane % kChunks) ^ (lr & 7);  // kRowsPer is 8: the row's low bits are lr
+  uint32_t vo[kL];
 #pragma unroll
-    for (int i = 0; i < kStripsA; ++i) {
-      const int c = tid + kThreads * i;
-      const int k = k0 + (c % kChunks) * 8, m = bm + c / kChunks;
-      const uint32_t oa = (m < M && k < K) ? (uint32_t)(((int64_t)m * K + k) * 2) : 0xFFFFFFF0u;
-      ga[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, oa, 0, 0);
-    }
+  for (int j = 0; j < kL; ++j) {
+    const int row = (j < kLA ? bm + (j * kWaves + wave) * kRowsPer : bn + ((j - kLA) * kWaves + wave) * kRowsPer) + lr;
+    vo[j] = row < (j < kLA ? M : N) ? (uint32_t)(((int64_t)row * K + lc * 8) * 2) : kOutside;
+  }
+  auto issue = [&](int s, int buf) {
+    unsigned char *base = smem + buf * kStage + wave * 1024;
+    const bool ragged = (s + 1) * kBK > K && s * kBK + lc * 8 >= K;
 #pragma unroll
-    for (int i = 0; i < kStripsW; ++i) {
-      const int c = tid + kThreads * i;
-      const int k = k0 + (c % kChunks) * 8, n = bn + c / kChunks;
-      const uint32_t ow = (n < N && k < K) ? (uint32_t)(((int64_t)n * K + k) * 2) : 0xFFFFFFF0u;
-      gw[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, ow, 0, 0);
-    }
-  };
-  auto stash = [&](int buf, const i32x4 (&ga)[kStripsA], const i32x4 (&gw)[kStripsW]) {
-#pragma unroll
-    for (int i = 0; i < kStripsA; ++i) {
-      const int c = tid + kThreads * i;
-      *reinterpret_cast<i32x4 *>(&sA[buf][(c / kChunks) * kLd + (c % kChunks) * 8]) = ga[i];
-    }
-#pragma unroll
-    for (int i = 0; i < kStripsW; ++i) {
-      const int c = tid + kThreads * i;
-      *reinterpret_cast<i32x4 *>(&sW[buf][(c / kChunks) * kLd + (c % kChunks) * 8]) = gw[i];
-    }
+    for (int j = 0; j < kL; ++j)
+      load_lds(j < kLA ? ra : rw, base + j * kWaves * 1024, ragged ? kOutside : vo[j], s * kBK * 2);
   };
 
   f32x4 acc[kTM][kTN];
@@ -112,98 +114,92 @@ __global__ void __launch_bounds__(64 * kWM * kWN) joint_proj_kernel(const uint16
 #pragma unroll
     for (int j = 0; j < kTN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  // K stages: stage s sits in LDS buffer s & 1 while it feeds the MFMAs; its
-  // global loads were issued two stages earlier into register set s & 1, so
-  // each load has two stages' compute to arrive in
   const int nk = (K + kBK - 1) / kBK;
-  i32x4 ga[2][kStripsA], gw[2][kStripsW];
-  fetch(0, ga[0], gw[0]);
-  stash(0, ga[0], gw[0]);
-  if (nk > 1) fetch(kBK, ga[1], gw[1]);
-  __syncthreads();
-  // fragment of a 16 x 32 operand tile: lane l holds row l % 16, K elements 8 * (l / 16) .. + 7
-  const int fr = lane & 15, fk = (lane >> 4) * 8;
-  auto stage = [&](int kt, auto set) {
-    constexpr int S = decltype(set)::value;  // = kt & 1
-    if (kt + 2 < nk) fetch((kt + 2) * kBK, ga[S], gw[S]);  // set S held stage kt, already in LDS
 #pragma unroll
-    for (int ks = 0; ks < kBK; ks += 32) {
+  for (int s = 0; s < kNB - 1; ++s)
+    if (s < nk) issue(s, s);
+  // fragment of a 16 x 32 operand tile: lane l holds row l % 16, K elements 8 * (l / 16) .. + 7
+  const int fr = lane & 15, fc = lane >> 4;
+  int buf = 0;
+  for (int s = 0; s < nk; ++s) {
+    // stage s has landed for every wave, and every wave is done reading the
+    // buffer of stage s - 1, which stage s + kNB - 1 is loaded into
+    if (s + kNB - 2 < nk) wait_barrier<(kNB - 2) * kL>();
+    else wait_barrier<0>();
+    if (s + kNB - 1 < nk) issue(s + kNB - 1, buf == 0 ? kNB - 1 : buf - 1);
+    const unsigned char *pa = smem + buf * kStage, *pw = pa + kBM * kBK * 2;
+#pragma unroll
+    for (int ks = 0; ks < kBK / 32; ++ks) {
       bf16x8 fa[kTM], fw[kTN];
 #pragma unroll
-      for (int i = 0; i < kTM; ++i) fa[i] = *reinterpret_cast<const bf16x8 *>(&sA[S][(wm + i * 16 + fr) * kLd + ks + fk]);
+      for (int j = 0; j < kTN; ++j)
+        fw[j] = *reinterpret_cast<const bf16x8 *>(pw + (wn + j * 16 + fr) * kBK * 2 + (((ks * 4 + fc) ^ (fr & 7)) * 16));
 #pragma unroll
-      for (int j = 0; j < kTN; ++j) fw[j] = *reinterpret_cast<const bf16x8 *>(&sW[S][(wn + j * 16 + fr) * kLd + ks + fk]);
+      for (int i = 0; i < kTM; ++i)
+        fa[i] = *reinterpret_cast<const bf16x8 *>(pa + (wm + i * 16 + fr) * kBK * 2 + (((ks * 4 + fc) ^ (fr & 7)) * 16));
 #pragma unroll
       for (int i = 0; i < kTM; ++i)
 #pragma unroll
-        for (int j = 0; j < kTN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fw[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < kTN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j], fa[i], acc[i][j], 0, 0, 0);
     }
-    if (kt + 1 < nk) stash(S ^ 1, ga[S ^ 1], gw[S ^ 1]);
-    __syncthreads();
-  };
-  for (int kt = 0; kt < nk; kt += 2) {
-    stage(kt, std::integral_constant<int, 0>{});
-    if (kt + 1 < nk) stage(kt + 1, std::integral_constant<int, 1>{});
+    buf = buf == kNB - 1 ? 0 : buf + 1;
   }
 
-  // accumulator of a 16 x 16 tile: lane l holds column l % 16, rows 4 * (l / 16) .. + 3
-  if (vec_out) {
-    // each 16-row slab of the wave's tile goes through the wave's own LDS area
-    // (the operand buffers are free after the last stage) and leaves as whole
-    // rows: 16 lanes store a row segment of 64 floats with 16-byte stores
-    constexpr int kSlabLd = kRN + 4;
-    float *slab = reinterpret_cast<float *>(smem) + wave * 16 * kSlabLd;
-    static_assert(sizeof(smem) >= sizeof(float) * 16 * kSlabLd * kWM * kWN, "LDS too small for the epilogue");
-    static_assert(kRN % 64 == 0, "the epilogue stores 64-column segments");
-    float bv[kTN];
+  // Epilogue.  In the accumulator of a 16 x 16 tile lane l holds output row l %
+  // 16, columns 4 * (l / 16) .. + 3.  Each 16-row slab of the wave's tile goes
+  // through the wave's own LDS area (free once every wave has read the last
+  // stage), chunks swizzled by the row as above, and leaves as whole row segments
+  // of kSeg columns, kRowsI rows a store.  The bias is fetched before the first
+  // store: a load behind stores would wait for all of them.
+  float bv[kRN / kSeg][4];
 #pragma unroll
-    for (int j = 0; j < kTN; ++j) {
-      const int n = bn + wn + j * 16 + (lane & 15);
-      bv[j] = (bias && n < N) ? bias[n] : 0.0f;
+  for (int sg = 0; sg < kRN / kSeg; ++sg)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int n = bn + wn + sg * kSeg + (lane % kLanes) * 4 + r;
+      bv[sg][r] = (bias && n < N) ? bias[n] : 0.0f;
     }
+  wait_barrier<0>();
+  f32x4 *slab = reinterpret_cast<f32x4 *>(smem) + wave * 16 * kLanes;
+  const int orow = lane / kLanes, ochunk = lane % kLanes;
 #pragma unroll
-    for (int i = 0; i < kTM; ++i) {
+  for (int i = 0; i < kTM; ++i) {
 #pragma unroll
-      for (int j = 0; j < kTN; ++j)
+    for (int sg = 0; sg < kRN / kSeg; ++sg) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) slab[((lane >> 4) * 4 + r) * kSlabLd + j * 16 + (lane & 15)] = acc[i][j][r] + bv[j];
+      for (int j = 0; j < kSeg / 16; ++j)
+        slab[fr * kLanes + ((j * 4 + fc) ^ (fr & (kLanes - 1)))] = acc[i][sg * (kSeg / 16) + j];
       __builtin_amdgcn_wave_barrier();
+      const int n = bn + wn + sg * kSeg + ochunk * 4;
 #pragma unroll
-      for (int sg = 0; sg < kRN / 64; ++sg) {
-        const int cn = bn + wn + sg * 64 + (lane & 15) * 4;  // first of the 4 columns this lane stores
+      for (int q = 0; q < 16 / kRowsI; ++q) {
+        const int row = q * kRowsI + orow;
+        const f32x4 x = slab[row * kLanes + (ochunk ^ (row & (kLanes - 1)))];
+        i32x4 v;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int row = q * 4 + (lane >> 4);
-          const f32x4 v = *reinterpret_cast<const f32x4 *>(&slab[row * kSlabLd + sg * 64 + (lane & 15) * 4]);
-          const int m = bm + wm + i * 16 + row;
-          // streaming stores: the logits are not read back by this kernel
-          if (m < M && cn < N) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(&out[(int64_t)m * N + cn]));
+        for (int r = 0; r < 4; ++r) v[r] = __float_as_int(x[r] + bv[sg][r]);
+        // a descriptor of this store's rows that exist; columns past N fall outside it
+        const int m0 = bm + wm + i * 16 + q * kRowsI;
+        const int rows = min(max(M - m0, 0), kRowsI);
+        const __amdgpu_buffer_rsrc_t ro = rsrc(out + (int64_t)m0 * N, (uint32_t)rows * (uint32_t)N * 4u);
+        const uint32_t o = ((uint32_t)orow * (uint32_t)N + (uint32_t)n) * 4u;
+        __builtin_amdgcn_raw_buffer_store_b128(v, ro, n + 3 < N ? o : kOutside, 0, kAux);
+        if (N % 4 != 0) {  // uniform: the row's last columns, one at a time
+#pragma unroll
+          for (int r = 0; r < 3; ++r)
+            __builtin_amdgcn_raw_buffer_store_b32(v[r], ro, (n + 3 >= N && n + r < N) ? o + 4 * r : kOutside, 0, kAux);
         }
       }
       __builtin_amdgcn_wave_barrier();
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < kTN; ++j) {
-      const int n = bn + wn + j * 16 + (lane & 15);
-      if (n >= N) continue;
-      const float bv = bias ? bias[n] : 0.0f;
-#pragma unroll
-      for (int i = 0; i < kTM; ++i) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = bm + wm + i * 16 + (lane >> 4) * 4 + r;
-          if (m < M) out[(int64_t)m * N + n] = acc[i][j][r] + bv;
-        }
-      }
     }
   }
 }
 
 // a launch shape of joint_proj_kernel
-template <int WM_, int WN_, int BK_, int TM_, int TN_>
+template <int WM_, int WN_, int TM_, int TN_, int NB_>
 struct ProjCfg {
-  static constexpr int WM = WM_, WN = WN_, BK = BK_, TM = TM_, TN = TN_;
+  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, NB = NB_;
+  static constexpr int BM = 16 * TM_ * WM_, BN = 16 * TN_ * WN_;
 };
 
 }  // namespace
@@ -220,21 +216,50 @@ extern "C" int joint_project(const uint16_t *A, const uint16_t *W, const float *
   if (M == 0) return FUSION_OK;
   if (!A || !W || !out) return set_error(FUSION_E_ARG, "NULL operand");
   if (((uintptr_t)A | (uintptr_t)W) % 16 != 0) return set_error(FUSION_E_ARG, "A and W must be 16-byte aligned");
-  // whole 16-byte row segments when every row starts 16-byte aligned
-  const int vec_out = (N % 4 == 0 && (uintptr_t)out % 16 == 0) ? 1 : 0;
+  auto tiles = [&](auto cfg) -> int64_t {
+    using C = decltype(cfg);
+    return (int64_t)((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
+  };
   auto go = [&](auto cfg) -> int {
     using C = decltype(cfg);
-    constexpr int BM = 16 * C::TM * C::WM, BN = 16 * C::TN * C::WN;
-    const int nct = (N + BN - 1) / BN, nrt = (M + BM - 1) / BM;
-    if ((int64_t)nct * nrt > 0x7FFFFFFFll) return set_error(FUSION_E_UNSUPPORTED, "too many tiles");
+    const int nct = (N + C::BN - 1) / C::BN, nrt = (M + C::BM - 1) / C::BM;
+    if (tiles(cfg) > 0x7FFFFFFFll) return set_error(FUSION_E_UNSUPPORTED, "too many tiles");
     const int xcd_map = (nrt % 4 == 0 && nct % 2 == 0) ? 1 : 0;
-    hipLaunchKernelGGL((joint_proj_kernel<C::WM, C::WN, C::BK, C::TM, C::TN>), dim3(nct * nrt), dim3(64 * C::WM * C::WN),
-                       0, stream, A, W, bias, M, N, K, nct, xcd_map, vec_out, out);
+    // Rows of whole 128-byte lines leave as streaming stores (nt with sc1: 472 us
+    // for 76800 x 4096 x 640, plain 553); rows that share lines with their
+    // neighbours are left for the L2 to merge (76800 x 1001 x 136: 91 us plain,
+    // over 100 streaming)
+    const dim3 grid(nct * nrt), block(64 * C::WM * C::WN);
+    if (N % 32 == 0)
+      hipLaunchKernelGGL((joint_proj_kernel<C::WM, C::WN, C::TM, C::TN, C::NB, 18>), grid, block, 0, stream, A, W, bias,
+                         M, N, K, nct, xcd_map, out);
+    else
+      hipLaunchKernelGGL((joint_proj_kernel<C::WM, C::WN, C::TM, C::TN, C::NB, 0>), grid, block, 0, stream, A, W, bias,
+                         M, N, K, nct, xcd_map, out);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? FUSION_OK : hip_error(e, "joint projection launch");
   };
-  // large batches (all frames at once): 256 x 256 tiles, 8 waves of 128 x 64;
-  // one frame's hypotheses (M of a few hundred): 64 x 64 tiles, 4 waves of 16 x
-  // 64, so that the launch still spreads over the CUs.  K stages of 32.
-  return M <= 4096 ? go(ProjCfg<4, 1, 64, 1, 4>{}) : go(ProjCfg<2, 4, 32, 8, 4>{});
+  // The largest tile that still gives every one of the 256 CUs work: a larger
+  // tile reads less LDS per multiply-accumulate, a smaller one fills the chip.
+  // Measured (us; tiles in brackets):
+  //              256x256      128x128      64x128       64x64        32x64
+  //   256x4096   19 [16]      9.6 [64]     7.5 [128]    6.2 [256]    6.1 [512]     K = 640
+  //   777x2500   12 [40]      7.2 [140]    6.7 [260]    7.8 [520]    7.3 [1000]    K = 256
+  //   1664x4096  21 [112]     13.3 [416]   16.7 [832]   20 [1664]    23 [3328]     K = 640
+  //   3328x1001  13 [52]      8.3 [208]    7.4 [416]    8.6 [832]    9.2 [1664]    K = 136
+  // 256 x 256 pays from about a thousand tiles and at short K, where a larger
+  // share of the time goes to the epilogue: 76800 x 4096 x 640 472 us against 489,
+  // 25600 x 2500 x 256 63 against 71, but 12800 x 8190 x 1024 260 against 235.
+  constexpr ProjCfg<2, 4, 8, 4, 2> t256{};
+  constexpr ProjCfg<2, 2, 4, 4, 2> t128{};
+  constexpr ProjCfg<2, 2, 2, 4, 3> t64x128{};
+  constexpr ProjCfg<2, 2, 2, 2, 4> t64{};
+  constexpr ProjCfg<2, 2, 1, 2, 4> t32{};
+  constexpr int64_t kCus = 256;
+  if (tiles(t256) >= 1000 && K <= 640) return go(t256);
+  if (tiles(t128) > kCus) return go(t128);
+  // (the narrower tiles store 8 rows at once: their offsets need 8 rows under 2 GiB)
+  if (tiles(t64x128) > kCus || N >= (1 << 25)) return go(t64x128);
+  if (tiles(t64) > kCus) return go(t64);
+  return go(t32);
 }

@@ -124,6 +124,17 @@ def test_projection_ragged_shapes(M, N, K):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(31, 4099, 72), (1100, 1030, 200), (2100, 1001, 136), (2200, 2050, 328),
+                                   (33001, 2050, 72), (32768, 2048, 640)])
+def test_projection_every_tile_shape(M, N, K):
+    """One size per tile shape of the dispatch, from 32 x 64 to 256 x 256, with ragged
+    rows, columns and last K stages (and one whole-tile size); sampled rows where large."""
+    A, W, bias = make_projection(5, M=M, N=N, K=K)
+    rows = np.random.default_rng(M + N + K).choice(M, size=min(M, 160), replace=False)
+    _check(A, W, bias, rows=np.unique(np.concatenate([rows, [0, M - 1]])))
+
+
+@pytest.mark.gpu
 def test_projection_full_c5_run_sampled_rows():
     # all 300 frames x 256 hypotheses in one launch (the shape bench.py times);
     # the oracle checks a sample of rows, every column
