@@ -5,6 +5,8 @@ from __future__ import annotations
 import glob
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -15,7 +17,6 @@ HIPCC_FLAGS = [
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     "-ffp-contract=off",  # one rounding per operation, as the fusion arithmetic is specified
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall",
@@ -31,11 +32,19 @@ def sources():
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + ".tmp"
-    cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
-           *sources(), "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc")]
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+
+    # one object per source, side by side: the fusion kernel's shapes are a file each
+    with tempfile.TemporaryDirectory(prefix="libfusion_") as objdir:
+        objs = {f: os.path.join(objdir, os.path.basename(f) + ".o") for f in sources()}
+        with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+            list(pool.map(lambda f: run([hipcc, *HIPCC_FLAGS, *inc, "-c", f, "-o", objs[f]]), objs))
+        run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs.values(), "-o", tmp])
     os.replace(tmp, LIB)
     return LIB
 
