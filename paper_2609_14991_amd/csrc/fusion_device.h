@@ -204,6 +204,137 @@ __device__ __forceinline__ void row_best(float &k, int &y) {
 // every outstanding vector-memory operation).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Orders a wave's own LDS writes before its later LDS reads by other lanes (one
+// wave's LDS operations complete in order; this keeps the compiler to it)
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+// The lane (below n <= 64) whose total has rank b, totals descending, lower lanes
+// first among equals; -1 if fewer than b + 1 lanes hold a total.  tot: every lane's
+// total in LDS (NaN: none), mine: this lane's.  Counting the totals ahead needs 16-byte
+// LDS reads and one compare each; equal totals show as a rank that no lane or
+// several lanes hold
+__device__ __forceinline__ int slot_holder(const double *tot, double mine, int n, int lane, int b) {
+  int gt = 0;
+  for (int q0 = 0; q0 < n; q0 += 16) {
+    double tv[16];
+#pragma unroll
+    for (int q = 0; q < 16; q += 2) {
+      const double2 d = *reinterpret_cast<const double2 *>(&tot[q0 + q]);
+      tv[q] = d.x;
+      tv[q + 1] = d.y;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) gt += (int)(tv[q] > mine);
+  }
+  const bool live = lane < n && mine == mine;
+  unsigned long long hold = __ballot(live && gt == b);
+  if (hold == 0ull && __popcll(__ballot(live)) > b) {
+    int r = gt;
+#pragma unroll 1
+    for (int j = 0; j < n; ++j) r += (int)(tot[j] == mine && j < lane);
+    hold = __ballot(live && r == b);
+  }
+  return hold ? __ffsll((long long)hold) - 1 : -1;
+}
+constexpr int kHashSlots = 512;
+// Beam recombination among n <= 64 Q candidates, Q per lane (lane, lane + 64, ..):
+// candidates of equal history hash merge into the first of them in candidate
+// order, whose total becomes the log-sum of theirs folded in that order; the
+// others' totals become NaN.  hash: this lane's (Q = 1; with Q > 1 they are in hh
+// already).  The first of each history is found through an LDS table: every candidate
+// lowers its hash's slot to its own index; those whose slot went to another
+// history try again with other bits of their hashes.  (Comparing all pairs took
+// n steps of several instructions on one wave.)  Then each round folds the next
+// member of every history at once
+template <int Q>
+__device__ __forceinline__ void merge_equal(double (&t)[Q], unsigned long long hash, int n, int lane, double *tot,
+                                            unsigned long long *hh, int *tab) {
+  const double none = __longlong_as_double(0x7FF8000000000000ll);
+  unsigned long long hq[Q];
+  int first[Q];
+  bool todo[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = q * 64 + lane;
+    todo[q] = t[q] == t[q];  // only candidates below n hold a total
+    hq[q] = Q == 1 ? hash : (todo[q] ? hh[i] : 0ull);
+    if (Q == 1) hh[i] = hash;
+    if (i < n) tot[i] = t[q];
+    first[q] = i;
+  }
+  for (int shift = 0;; shift += 9) {
+    unsigned long long open = 0ull;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) open |= __ballot(todo[q]);
+    if (open == 0ull) break;
+#pragma unroll
+    for (int e = 0; e < kHashSlots; e += 256) *reinterpret_cast<int4 *>(&tab[e + lane * 4]) = make_int4(INT_MAX, INT_MAX, INT_MAX, INT_MAX);
+    wave_lds_sync();
+    int sl[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      // (after the hash's 48 bits are used up, the slot is the candidate's rank among
+      // all: mixed hashes never come to that)
+      sl[q] = (int)((shift < 45 ? hq[q] >> shift : hq[q] * 0x9E3779B97F4A7C15ull >> (shift % 50)) & (kHashSlots - 1));
+      if (todo[q]) atomicMin(&tab[sl[q]], q * 64 + lane);
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (todo[q]) {
+        const int f = tab[sl[q]];
+        if (hh[f] == hq[q]) {
+          first[q] = f;
+          todo[q] = false;
+        }
+      }
+    }
+    wave_lds_sync();
+  }
+  // members other than the first, next in order
+  bool member[Q];
+  unsigned long long left = 0ull;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    member[q] = first[q] != q * 64 + lane;
+    left |= __ballot(member[q]);
+  }
+  if (left == 0ull) return;
+  bool lead[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) lead[q] = !member[q] && t[q] == t[q];
+  bool gone[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) gone[q] = member[q];
+  while (left) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (lead[q]) tab[q * 64 + lane] = INT_MAX;
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (member[q]) atomicMin(&tab[first[q]], q * 64 + lane);
+    wave_lds_sync();
+    left = 0ull;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int nx = lead[q] ? tab[q * 64 + lane] : INT_MAX;
+      if (__ballot(nx != INT_MAX)) {
+        if (nx != INT_MAX) t[q] = log_add(t[q], tot[nx]);
+      }
+      if (member[q] && tab[first[q]] == q * 64 + lane) member[q] = false;
+      left |= __ballot(member[q]);
+    }
+    wave_lds_sync();
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (gone[q]) t[q] = none;
+}
+
 // hypothesis state carried between frames (LDS, written by one lane)
 template <int NL>
 struct HypState {
@@ -220,7 +351,7 @@ struct HypState {
 
 
 template <int W, int NC, int KM, bool AL, int MODE, int NL>
-__global__ void __launch_bounds__(W) fusion_kernel(Params p) {
+__global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   constexpr int NW = W / 64;
   constexpr int Vp = NC * 4 * W;
   constexpr int kUA = W >= 1024 ? 1 : 4;  // arcs per lane fetched in the second hop
@@ -258,19 +389,23 @@ __global__ void __launch_bounds__(W) fusion_kernel(Params p) {
   __shared__ int w_y[kMaxWaves][KM];
   // each wave's best key with its wave index, and the hypothesis' listed entries
   // (compacted) and top K, all as sel_order composites (KM > 1)
-  __shared__ __align__(16) unsigned long long s_wmax[kMaxWaves];
+  __shared__ __align__(16) int s_wmax[kMaxWaves];
   __shared__ __align__(16) unsigned long long s_sel[16];
   __shared__ unsigned long long s_win[KM];
   __shared__ HypState<NL> hs;
   // beam rendezvous staging (wave 0): candidate records (the second LM's source
   // and c_1 in s_xb), parent flags, totals
-  __shared__ int4 s_xa[FUSION_MAX_BEAM * FUSION_MAX_K];
-  __shared__ int2 s_xb[NL > 1 ? FUSION_MAX_BEAM * FUSION_MAX_K : 1];
-  __shared__ int s_xf[FUSION_MAX_BEAM * FUSION_MAX_K];
-  __shared__ __align__(16) double s_tot[FUSION_MAX_BEAM * FUSION_MAX_K];
-  // recombination: history hash after each candidate, merged totals
-  __shared__ unsigned long long s_hh[MODE == kModeBeamRC ? FUSION_MAX_BEAM * FUSION_MAX_K : 1];
-  __shared__ double s_mt[MODE == kModeBeamRC ? FUSION_MAX_BEAM * FUSION_MAX_K : 1];
+  constexpr bool RCM = MODE == kModeBeamRC || MODE == kModeBeamRCWide;
+  constexpr int kCand = MODE == kModeBeamWide || MODE == kModeBeamRCWide ? FUSION_MAX_BEAM * FUSION_MAX_K : 64;
+  constexpr int kStaged = kCand > 64 ? kCand : 1;
+  __shared__ int4 s_xa[kStaged];
+  __shared__ int2 s_xb[NL > 1 ? kStaged : 1];
+  __shared__ int s_xf[kStaged];
+  __shared__ __align__(16) double s_tot[kCand];
+  // recombination: history hash after each candidate, the table that groups them
+  __shared__ unsigned long long s_hh[RCM ? kCand : 1];
+  __shared__ __align__(16) int s_tab[RCM ? kHashSlots : 4];
+  __shared__ int s_surv[64];  // beams of more than 64 candidates: those left to rank
   __shared__ long long s_sbase[NL][kMaxLevels];  // state id of arc index i of level L < N-1: s_sbase[L] + i
   __shared__ int s_lbeg[NL][kMaxLevels];  // first arc of each level of the current state
   __shared__ int s_cfg[2];  // V, blank: re-read each frame so per-token masks stay inside the loop
@@ -295,8 +430,9 @@ __global__ void __launch_bounds__(W) fusion_kernel(Params p) {
   };
   const int wave = g >> 6;
   const int lane = g & 63;
-  constexpr bool BEAM = MODE == kModeBeam || MODE == kModeBeamRC;
-  constexpr bool RC = MODE == kModeBeamRC;
+  constexpr bool BEAM = MODE >= kModeBeam;
+  constexpr bool RC = RCM;
+  constexpr bool WIDE = MODE == kModeBeamWide || MODE == kModeBeamRCWide;  // more than 64 candidates a stream
   const int B = BEAM ? p.B : 1, K = p.k;
   int Nl[NL], RSl[NL];  // order and record stride of each LM
 #pragma unroll
@@ -902,19 +1038,33 @@ __global__ void __launch_bounds__(W) fusion_kernel(Params p) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) lb = max(lb, max(max(sk[c][0], sk[c][1]), max(sk[c][2], sk[c][3])));
         const int mw = wave_max_i(lb);
-        if (lane == 0) s_wmax[wave] = sel_order(mw, wave);
+        // (the wave index in the low bits makes the maxima distinct; tau, with them
+        // cleared, can only be lower, which keeps it a valid bound)
+        if (lane == 0) s_wmax[wave] = (mw & ~15) | (15 - wave);
         lds_barrier();
         int tau = INT_MIN;
         if (NW >= K) {
-          // the K-th largest of the NW maxima (counted with multiplicity): lane
-          // l < NW ranks maximum l among all of them (ties by wave index) and the
-          // lane of rank K-1 holds it
-          const unsigned long long mine = s_wmax[lane < NW ? lane : 0];
+          // the K-th largest of the NW maxima: lane l < NW counts those ahead of
+          // maximum l and the lane of rank K-1 holds it
+          const int mine = s_wmax[lane & (NW - 1)];
+          int wm[kMaxWaves];
+#pragma unroll
+          for (int w2 = 0; w2 < NW; w2 += (NW >= 4 ? 4 : 1)) {
+            if constexpr (NW >= 4) {
+              const int4 d = *reinterpret_cast<const int4 *>(&s_wmax[w2]);
+              wm[w2] = d.x;
+              wm[w2 + 1] = d.y;
+              wm[w2 + 2] = d.z;
+              wm[w2 + 3] = d.w;
+            } else {
+              wm[w2] = s_wmax[w2];
+            }
+          }
           int r = 0;
 #pragma unroll
-          for (int w2 = 0; w2 < NW; ++w2) r += (int)(s_wmax[w2] > mine);
+          for (int w2 = 0; w2 < NW; ++w2) r += (int)(wm[w2] > mine);
           const unsigned long long at = __ballot(lane < NW && r == K - 1);
-          tau = sel_key(__builtin_amdgcn_readlane((int)(mine >> 32), __ffsll((long long)at) - 1));
+          tau = __builtin_amdgcn_readlane(mine, __ffsll((long long)at) - 1) & ~15;
         }
         // survivors: keys >= tau, never a non-candidate (INT_MIN; every real key,
         // -inf included, maps above it)
@@ -1051,7 +1201,7 @@ __global__ void __launch_bounds__(W) fusion_kernel(Params p) {
     // over the lanes (entry j of wave w is element e = j*NW + w, lane e % 64, slot
     // e / 64); K rounds of a wave maximum, ties to the lowest id -------------------
     if (wave == 0) {
-      constexpr int kSlots = (kMaxWaves * KM + 63) / 64;
+      constexpr int kSlots = (NW * KM + 63) / 64;
       int ek[kSlots], ey[kSlots];
 #pragma unroll
       for (int q = 0; q < kSlots; ++q) {
@@ -1063,18 +1213,27 @@ __global__ void __launch_bounds__(W) fusion_kernel(Params p) {
       // candidate j ends in lane j
       int ck = INT_MIN, cy = INT_MAX;
       bool picked = false;
-      if constexpr (kSlots == 1 && KM > 1) {
+      if constexpr (KM > 1) {
         // at most 16 listed entries (the usual case after the wave-level
         // narrowing): compact them into LDS, let each count the entries ahead
         // of it (key desc, then id asc) in registers, and place it by that rank
-        const bool valid = ek[0] != INT_MIN;
-        const unsigned long long vb = __ballot(valid);
-        const int n = __popcll(vb);
+        unsigned long long vb[kSlots];
+        int n = 0;
+#pragma unroll
+        for (int q = 0; q < kSlots; ++q) {
+          vb[q] = __ballot(ek[q] != INT_MIN);
+          n += __popcll(vb[q]);
+        }
         if (n <= 16) {
-          const int pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(vb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vb, 0u));
           // an entry is ahead of another exactly when its composite is larger;
           // padding (0) is never ahead of a listed entry (every key is above INT_MIN)
-          if (valid) s_sel[pos] = sel_order(ek[0], ey[0]);
+          int base = 0;
+#pragma unroll
+          for (int q = 0; q < kSlots; ++q) {
+            const int pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(vb[q] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vb[q], 0u));
+            if (ek[q] != INT_MIN) s_sel[pos] = sel_order(ek[q], ey[q]);
+            base += __popcll(vb[q]);
+          }
           if (lane >= n && lane < 16) s_sel[lane] = 0ull;
           // one wave: its LDS operations complete in order
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1243,12 +1402,13 @@ __global__ void __launch_bounds__(W) fusion_kernel(Params p) {
         }
         // every workgroup of the stream ranks the same B*k candidates by (total
         // desc, parent asc, rank asc), i.e. candidate order breaks ties; slot b
-        // takes rank b.  The totals are staged in LDS (NaN: no candidate, never
-        // ahead of anything) and each lane counts the candidates ahead of its own.
+        // takes rank b (NaN: no candidate, never ahead of anything)
         const int nc = B * K;
-        for (int i0 = 0; i0 < nc; i0 += 64) {
-          const int i = i0 + lane;
-          unsigned long long w[XW];
+        const double kNone = __longlong_as_double(0x7FF8000000000000ll);
+        const int64_t o = (int64_t)t * H + h;
+        // the record of candidate i (i < nc): waits until all its words carry this
+        // frame's tag; false if the wait ran out
+        auto poll = [&](int i, unsigned long long (&w)[XW]) -> bool {
 #pragma unroll
           for (int q = 0; q < XW; ++q) w[q] = 0ull;
           bool cur = i >= nc;
@@ -1267,162 +1427,150 @@ __global__ void __launch_bounds__(W) fusion_kernel(Params p) {
               break;
             }
           }
-          if (i < nc) {
-            const int y1 = (int)((w[2] >> 32) & 0xFFFF);
-            const bool valid = cur && y1 != 0;
-            s_xa[i] = make_int4(y1 - 1, (int)(unsigned)((w[1] >> 16) & 0xFFFFFFFFull), (int)(unsigned)(w[2] & 0xFFFFFFFFull),
-                                (int)(w[3] & 0xFFFF) - 1);
-            s_xf[i] = (int)((w[3] >> 16) & 0xFF);
-            if constexpr (NL > 1)
-              s_xb[i] = make_int2((int)(unsigned)(w[4] & 0xFFFFFFFFull), (int)((w[4] >> 32) & 0xFFFF) - 1);
-            if constexpr (RC) s_hh[i] = w[XW - 1] & kPay;
-            s_tot[i] = valid ? __longlong_as_double((long long)((w[0] & kPay) | ((w[1] & 0xFFFF) << 48)))
-                             : __longlong_as_double(0x7FF8000000000000ll);
-          } else if (i < 16) {
-            s_tot[i] = __longlong_as_double(0x7FF8000000000000ll);  // unused: never ahead
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if constexpr (RC) {
-          // recombination: candidates that reach the same history (equal hash)
-          // merge into the first of them in candidate order, with the log-sum
-          // of their totals folded in that order; the others leave the ranking
-          if (nc <= 64) {
-            // one candidate per lane, every other candidate's total and hash
-            // read from its lane (readlane), not from LDS
-            const double ti = lane < nc ? s_tot[lane] : __longlong_as_double(0x7FF8000000000000ll);
-            const unsigned long long hi = lane < nc ? s_hh[lane] : 0ull;
-            const long long tb = __double_as_longlong(ti);
-            int first = -1;
-            double acc = 0.0;
-            for (int j = 0; j < nc; ++j) {
-              const double tj = __longlong_as_double(
-                  ((long long)(unsigned)__builtin_amdgcn_readlane((int)(tb >> 32), j) << 32) |
-                  (long long)(unsigned)__builtin_amdgcn_readlane((int)tb, j));
-              const unsigned long long hj =
-                  ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(hi >> 32), j) << 32) |
-                  (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)hi, j);
-              if (ti == ti && tj == tj && hj == hi) {
-                if (first < 0) {
-                  first = j;
-                  acc = tj;
-                } else {
-                  acc = log_add(acc, tj);
-                }
-              }
-            }
-            // every lane has read its own entry before any lane writes
-            if (lane < nc) s_tot[lane] = (ti == ti && first == lane) ? acc : __longlong_as_double(0x7FF8000000000000ll);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-          } else {
-#pragma unroll 1
-            for (int i = lane; i < nc; i += 64) {
-              double m = __longlong_as_double(0x7FF8000000000000ll);
-              const double ti = s_tot[i];
-              if (ti == ti) {
-                const unsigned long long hi = s_hh[i];
-                int first = -1;
-                double acc = 0.0;
-#pragma unroll 1
-                for (int j = 0; j < nc; ++j) {
-                  const double tj = s_tot[j];
-                  if (tj == tj && s_hh[j] == hi) {
-                    if (first < 0) {
-                      first = j;
-                      acc = tj;
-                    } else {
-                      acc = log_add(acc, tj);
-                    }
-                  }
-                }
-                if (first == i) m = acc;
-              }
-              s_mt[i] = m;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-#pragma unroll 1
-            for (int i = lane; i < nc; i += 64) s_tot[i] = s_mt[i];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-          }
-        }
-        int wi = -1;
-        bool ranked = false;
-        if (nc <= 16) {
-          // up to 16 candidates (B * k <= 16; entries nc..15 hold NaN): every
-          // lane loads all totals at once (eight 16-byte reads) and counts
-          // those ahead of its own in registers; equal totals need the
-          // candidate-order rule and take the general count below
-          double tv[16];
-#pragma unroll
-          for (int q = 0; q < 16; q += 2) {
-            const double2 d = *reinterpret_cast<const double2 *>(&s_tot[q]);
-            tv[q] = d.x;
-            tv[q + 1] = d.y;
-          }
-          const double ti = s_tot[lane & 15];
-          int gt = 0, eq = 0;
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            gt += (int)(tv[q] > ti);
-            eq += (int)(tv[q] == ti);
-          }
-          const bool live = lane < nc && ti == ti;
-          if (__ballot(live && eq > 1) == 0ull) {
-            if (live && gt == b) wi = lane;
-            ranked = true;
-          }
-        }
-        for (int i = (ranked ? 64 : 0) + lane; i < nc; i += 64) {
-          const double ti = s_tot[i];
-          if (ti == ti) {
-            int r = 0;
-#pragma unroll 16
-            for (int j = 0; j < nc; ++j) {
-              const double tj = s_tot[j];
-              r += (tj > ti || (tj == ti && j < i)) ? 1 : 0;
-            }
-            if (r == b) wi = i;
-          }
-        }
-        const int64_t o = (int64_t)t * H + h;
-        if (wi >= 0) {
-          // the lane holding the slot's candidate installs it
-          const int4 a = s_xa[wi];
-          const int xf = s_xf[wi];
-          const double tot = s_tot[wi];
-          int2 xb = make_int2(0, 0);
-          if constexpr (NL > 1) xb = s_xb[wi];
-          const int y = a.x;
+          return cur;
+        };
+        // the hypothesis of this slot becomes candidate i, of record fields src0 ..
+        auto install = [&](int i, double tot, int y, int src0, int c1p0, int qs, int xf, int src1, int c1p1,
+                           unsigned long long hist) {
           int src[NL], c1p[NL];
-          src[0] = a.y;
-          c1p[0] = a.w;
+          src[0] = src0;
+          c1p[0] = c1p0;
           if constexpr (NL > 1) {
-            src[1] = xb.x;
-            c1p[1] = xb.y;
+            src[1] = src1;
+            c1p[1] = c1p1;
           }
 #pragma unroll
-          for (int i = 0; i < NL; ++i) {
-            hs.lmsrc[i] = src[i];
-            hs.c1p[i] = c1p[i];
-            hs.c1[i] = y != blank ? y : c1p[i];
+          for (int l = 0; l < NL; ++l) {
+            hs.lmsrc[l] = src[l];
+            hs.c1p[l] = c1p[l];
+            hs.c1[l] = y != blank ? y : c1p[l];
           }
-          hs.qsrc = a.z;
+          hs.qsrc = qs;
           hs.y = y;
           hs.fl = 1 | (xf & 2);
-          if constexpr (RC) hs.hist = s_hh[wi];
+          if constexpr (RC) hs.hist = hist;
           hs.S = tot;
           p.tokens[o] = y;
-          p.parents[o] = wi / K;
+          p.parents[o] = i / K;
+        };
+        auto tot_of = [&](const unsigned long long (&w)[XW]) {
+          return __longlong_as_double((long long)((w[0] & kPay) | ((w[1] & 0xFFFF) << 48)));
+        };
+        bool taken;  // some candidate reaches this slot
+        if constexpr (!WIDE) {
+          // one candidate per lane: the record stays in its lane's registers, from
+          // where the winner installs it; only the totals pass through LDS
+          unsigned long long w[XW];
+          const bool cur = poll(lane, w);
+          const int y1 = (int)((w[2] >> 32) & 0xFFFF);
+          double ti = (cur && y1 != 0) ? tot_of(w) : kNone;
+          if constexpr (RC) {
+            double tm[1] = {ti};
+            merge_equal<1>(tm, w[XW - 1] & kPay, nc, lane, s_tot, s_hh, s_tab);
+            ti = tm[0];
+          }
+          s_tot[lane] = ti;
+          wave_lds_sync();
+          const int r = slot_holder(s_tot, ti, nc, lane, b);
+          taken = r >= 0;
+          if (lane == r)
+            install(lane, ti, y1 - 1, (int)(unsigned)((w[1] >> 16) & 0xFFFFFFFFull), (int)(w[3] & 0xFFFF) - 1,
+                    (int)(unsigned)(w[2] & 0xFFFFFFFFull), (int)((w[3] >> 16) & 0xFF),
+                    NL > 1 ? (int)(unsigned)(w[NL > 1 ? 4 : 0] & 0xFFFFFFFFull) : 0,
+                    NL > 1 ? (int)((w[NL > 1 ? 4 : 0] >> 32) & 0xFFFF) - 1 : 0, w[XW - 1] & kPay);
+        } else {
+          // four candidates per lane (lane, lane + 64, ..), staged in LDS
+          double tq[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            tq[q] = kNone;
+            const int i = q * 64 + lane;
+            if (q * 64 >= nc) continue;  // uniform
+            unsigned long long w[XW];
+            const bool cur = poll(i, w);
+            if (i < nc) {
+              const int y1 = (int)((w[2] >> 32) & 0xFFFF);
+              s_xa[i] = make_int4(y1 - 1, (int)(unsigned)((w[1] >> 16) & 0xFFFFFFFFull),
+                                  (int)(unsigned)(w[2] & 0xFFFFFFFFull), (int)(w[3] & 0xFFFF) - 1);
+              s_xf[i] = (int)((w[3] >> 16) & 0xFF);
+              if constexpr (NL > 1)
+                s_xb[i] = make_int2((int)(unsigned)(w[4] & 0xFFFFFFFFull), (int)((w[4] >> 32) & 0xFFFF) - 1);
+              if constexpr (RC) s_hh[i] = w[XW - 1] & kPay;
+              if (cur && y1 != 0) tq[q] = tot_of(w);
+            }
+          }
+          if constexpr (RC) merge_equal<4>(tq, 0ull, nc, lane, s_tot, s_hh, s_tab);
+          // The best B are among the candidates at or above any bound that at least B
+          // of them reach: here just below the least of the parents' best totals
+          // (candidate 0 of each parent's k), which leaves little more than B.
+          // Those, in candidate order, are ranked one per lane
+          float least = INFINITY;
+          int nv = 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int i = q * 64 + lane;
+            if (i < nc && i % K == 0 && tq[q] == tq[q]) least = fminf(least, (float)tq[q]);
+            nv += __popcll(__ballot(tq[q] == tq[q]));
+          }
+          least = -wave_max_f(-least);
+          const double bound = (double)(least - fabsf(least) * 1e-6f);
+          unsigned long long up[4];
+          int ns = 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            up[q] = __ballot(tq[q] >= bound);
+            ns += __popcll(up[q]);
+          }
+          int wi = -1;
+          if (ns <= 64 && (ns >= B || ns == nv)) {
+            s_tot[lane] = kNone;
+            wave_lds_sync();
+            int base = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int at = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(up[q] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)up[q], 0u));
+              if (tq[q] >= bound) {
+                s_tot[at] = tq[q];
+                s_surv[at] = q * 64 + lane;
+              }
+              base += __popcll(up[q]);
+            }
+            wave_lds_sync();
+            const int r = slot_holder(s_tot, s_tot[lane], ns, lane, b);
+            if (r >= 0) wi = s_surv[r];
+          } else {
+            // many candidates at or near one total, or few parents left: rank all
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (q * 64 + lane < nc) s_tot[q * 64 + lane] = tq[q];
+            wave_lds_sync();
+#pragma unroll 1
+            for (int i = lane; i < nc; i += 64) {
+              const double ti = s_tot[i];
+              int r = ti == ti ? 0 : INT_MIN;
+#pragma unroll 8
+              for (int j = 0; j < nc; ++j) {
+                const double tj = s_tot[j];
+                r += (tj > ti || (tj == ti && j < i)) ? 1 : 0;
+              }
+              if (r == b) wi = i;
+            }
+            const unsigned long long m = __ballot(wi >= 0);
+            if (m) wi = __builtin_amdgcn_readlane(wi, __ffsll((long long)m) - 1);
+          }
+          taken = wi >= 0;
+          double tw = kNone;  // the winner's total, from its lane
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (wi == q * 64 + lane) tw = tq[q];
+          if (taken && lane == (wi & 63)) {
+            const int4 c = s_xa[wi];
+            int2 xb = make_int2(0, 0);
+            if constexpr (NL > 1) xb = s_xb[wi];
+            install(wi, tw, c.x, c.y, c.w, c.z, s_xf[wi], xb.x, xb.y, RC ? s_hh[RC ? wi : 0] : 0ull);
+          }
         }
-        if (__ballot(wi >= 0) == 0ull && lane == 0) {
+        if (!taken && lane == 0) {
           // no candidate reaches this slot: the hypothesis is dead and keeps its state
 #pragma unroll
           for (int i = 0; i < NL; ++i) {
@@ -1476,6 +1624,11 @@ KernelFn pick_mode(int mode) {
     if (mode == kModeGreedy) return fusion_kernel<W, NC, KM, AL, kModeGreedy, NL>;
   }
   if (mode == kModeBeamRC) return fusion_kernel<W, NC, KM, AL, kModeBeamRC, NL>;
+  // (more than 64 candidates need k > 1 even at the widest beam)
+  if constexpr (KM > 1) {
+    if (mode == kModeBeamWide) return fusion_kernel<W, NC, KM, AL, kModeBeamWide, NL>;
+    if (mode == kModeBeamRCWide) return fusion_kernel<W, NC, KM, AL, kModeBeamRCWide, NL>;
+  }
   return mode == kModeStep ? fusion_kernel<W, NC, KM, AL, kModeStep, NL> : fusion_kernel<W, NC, KM, AL, kModeBeam, NL>;
 }
 template <int W, int NC, int KM, int NL>

@@ -172,7 +172,8 @@ int launch(Params &p, int n_hyp, hipStream_t stream, unsigned long long *fixed =
   const Shape sh = shape_for(p.V);
   const int km = p.k <= 1 ? 1 : p.k <= 4 ? 4 : 8;
   const bool al = (p.V % 4 == 0) && ((uintptr_t)p.logits % 16 == 0) && (!p.fused || (uintptr_t)p.fused % 16 == 0);
-  const int mode = p.step_mode ? kModeStep : p.B == 1 ? kModeGreedy : p.recombine ? kModeBeamRC : kModeBeam;
+  const int mode = p.step_mode ? kModeStep : p.B == 1 ? kModeGreedy : p.B * p.k > 64 ? (p.recombine ? kModeBeamRCWide : kModeBeamWide)
+                                                             : (p.recombine ? kModeBeamRC : kModeBeam);
   KernelFn fn = pick(sh, km, al, mode, p.n_lm);
   if (!fn) return set_error(FUSION_E_UNSUPPORTED, "two LMs need V <= 4096");
   const DeviceInfo di = device_info();

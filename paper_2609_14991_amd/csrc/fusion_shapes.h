@@ -10,8 +10,6 @@
 namespace fusion {
 
 struct Params {
-  LMDevice lm[FUSION_MAX_LMS];  // the n_lm models of Eq. (1), each with its own weight lam[i]
-  TrieDevice tr;
   const float *logits;
   int32_t *lm_state;
   int32_t *boost_state;
@@ -32,6 +30,8 @@ struct Params {
   int32_t T, S, B, V, k, blank, mode, has_trie, step_mode, s_off, n_str, xcd_map, n_lm, recombine, t_base;
   float lam[FUSION_MAX_LMS], beta;
   int *status;  // this GPU's status word (bits ORed in by workgroups that meet a bad state or a failed wait)
+  LMDevice lm[FUSION_MAX_LMS];  // the n_lm models of Eq. (1), each with its own weight lam[i]
+  TrieDevice tr;
 };
 
 typedef void (*KernelFn)(Params);
@@ -42,8 +42,10 @@ struct Shape {
 };
 
 // MODE: what a launch computes (the code of the other modes is compiled out)
-// (kModeBeamRC: beam with recombination of equal histories)
-constexpr int kModeStep = 0, kModeGreedy = 1, kModeBeam = 2, kModeBeamRC = 3;
+// (RC: with recombination of equal histories; Wide: more than 64 candidates per
+// stream, several per lane, staged in LDS: in one kernel with the others, that
+// code made the 64 x 4 beam of 4096 tokens spill and run 3 % longer)
+constexpr int kModeStep = 0, kModeGreedy = 1, kModeBeam = 2, kModeBeamRC = 3, kModeBeamWide = 4, kModeBeamRCWide = 5;
 
 constexpr int kAux = 256;                     // LDS side tables: phrase transitions, top-level next states
 

@@ -180,3 +180,39 @@ def test_beam_exact_ties(lam_beta):
     fin = np.isfinite(r["hyp_score"])
     assert np.array_equal(np.isfinite(sc.cpu().numpy()), fin)
     assert np.abs(sc.cpu().numpy()[fin] - r["hyp_score"][fin]).max() <= T * SCORE_TOL
+
+
+@pytest.mark.parametrize("B,k", [(2, 4), (8, 8), (17, 4), (16, 8), (32, 8)])
+@pytest.mark.parametrize("recombine", [False, True])
+def test_candidate_ranking_with_ties(B, k, recombine):
+    """One and several candidates per lane of the merge (up to and beyond 64), on
+    integer logits that are the same for every slot of a stream, so that paths in
+    another order tie exactly across parents; with recombination those ties are
+    histories to merge.  Free-running without it, replayed by the oracle with it."""
+    V, S, T = 90, 3, 10
+    rng, lm, ph = models(V, B * k)
+    glm, gtr = F.ngram_load_arrays(lm), F.boost_build_phrases(V, 0, ph)
+    x = np.repeat(rng.integers(-2, 3, size=(T, S, V)).astype(np.float32), B, axis=1)
+    lam, beta = (0.5, 0.5) if recombine else (0.0, 0.0)
+    H = S * B
+    ls = torch.full((1, H), V, dtype=torch.int32, device=dev())
+    bs = torch.zeros((H,), dtype=torch.int32, device=dev())
+    sc0 = np.tile(np.array([0.0] + [-np.inf] * (B - 1)), S)
+    sc = torch.from_numpy(sc0.copy()).to(dev())
+    out = F.run_lms([glm], [lam], gtr, torch.from_numpy(x).to(dev()), S, B, k, beta, 0, F.FUSION_BLANK_COMPETE, ls, bs,
+                    sc, recombine=recombine)
+    torch.cuda.synchronize()
+    assert F.fusion_device_status() == 0
+    tok, par = out["tokens"].cpu().numpy(), out["parents"].cpu().numpy()
+    forced = dict(forced_tokens=tok, forced_parents=par, tol=TIE_TOL) if recombine else {}
+    r = oracle.run_lms([oracle.OracleLM(lm)], [lam], oracle.OracleTrie(V, 0, ph), x, S, B, k, beta, 0, 1, [[V] * H],
+                       [0] * H, sc0, threads=4, recombine=recombine, **forced)
+    if recombine:
+        assert (r["mismatch_at"] < 0).all()
+    else:
+        assert np.array_equal(tok, r["tokens"]) and np.array_equal(par, r["parents"])
+    assert np.array_equal(ls.cpu().numpy().reshape(-1), np.asarray(r["lm_state"]).reshape(-1))
+    assert np.array_equal(bs.cpu().numpy(), r["boost_state"])
+    fin = np.isfinite(r["hyp_score"])
+    assert np.array_equal(np.isfinite(sc.cpu().numpy()), fin)
+    assert np.abs(sc.cpu().numpy()[fin] - r["hyp_score"][fin]).max() <= T * SCORE_TOL
