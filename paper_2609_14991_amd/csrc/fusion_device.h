@@ -345,6 +345,7 @@ struct HypState {
   int lmsrc[NL], c1p[NL], c1[NL], cur_lm[NL];
   int qsrc, y, fl;  // phrase source, token; flags 1 alive, 2 invalid
   int cur_q;        // phrase state scored this frame
+  int same;         // greedy: the state of the frame before (blank emitted), whose rows in LDS still hold
   double S;         // running beam score
   unsigned long long hist;  // 48-bit hash of the history (initial states, emitted tokens): recombination
 };
@@ -362,15 +363,16 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   // explicit arc (stamp << 48 | level << 45 | offset << 32 | value bits, kept by
   // an atomic max, so the highest level wins whatever the order of the writes);
   // the phrase transition overriding the root's (stamp << 16 | transition + 1).
-  // The stamp is the frame's (t mod 2^15) + 1: entries of earlier frames compare
-  // lower and read as absent, so no per-frame clearing is needed.  Row NL of
+  // The stamp is the number of rows assembled so far: entries of earlier rows
+  // compare lower and read as absent, so nothing is cleared per frame.  Row NL of
   // lmval holds the first LM's context row when its state has one: the LM row of
   // the deepest context of the chain with many successors, already resolved
   // through every level up to that context
   // With one LM the phrase term reads erow: per token the entry value E of the
   // phrase state after it, the root's unless this frame's phrase state
   // overrides the token.  Each lane puts its tokens back to the root's values
-  // right after reading them, and the scatter writes the overrides.
+  // right after reading them, and the scatter writes the overrides; a frame that
+  // keeps its rows finds them through ptag instead.
   constexpr bool ER = NL == 1 && NC == 1;  // (8192-wide rows: no room in the LDS)
   constexpr int kRows = NL + (CTX ? 1 : 0);
   float *lmval = reinterpret_cast<float *>(dyn);                                                  // [kRows][Vp]
@@ -385,6 +387,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   __shared__ float s_lse;  // the current frame's log-sum-exp of the logits row
   __shared__ int s_am;     // and the lowest id holding its maximum
   __shared__ int s_nstat;  // waves done with the next frame's strip statistics
+  __shared__ unsigned s_emit[2];  // greedy: which of 64 frames blank does not take
   __shared__ int w_key[kMaxWaves][KM];  // order-preserving images of the keys (ord_key)
   __shared__ int w_y[kMaxWaves][KM];
   // each wave's best key with its wave index, and the hypothesis' listed entries
@@ -514,6 +517,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     hs.y = -1;
     hs.fl = (alive ? 1 : 0) | ((ok_lm && ok_q) ? 0 : 2);
     hs.cur_q = q;
+    hs.same = 0;
     hs.S = sc;
     if constexpr (RC) {
       // the history carried from an earlier call, else one that starts at the
@@ -561,8 +565,82 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   };
   // the logits row of this hypothesis at the frame being fetched; it advances by
   // one frame (H rows) per fetch and stays on the last frame
-  const float *xrow = p.logits + (int64_t)h * p.V;
   const int64_t xstride = (int64_t)H * p.V;
+  // Greedy mode A: a frame whose raw argmax is blank emits blank whatever the LM and
+  // the phrases say and changes no state, so the frame loop passes it over (unless
+  // fused rows or the byte count need its scores).  Which frames those are depends
+  // on the logits alone: 64 frames at a time are looked through ahead of the loop,
+  // each wave reading whole rows, several in flight.  The row statistics then serve
+  // no purpose (a greedy decision compares keys) and are left out too.  285 greedy
+  // streams of 63 speech-like frames, half of them blank: 261 us before, 140 after
+  constexpr bool GR = MODE == kModeGreedy;
+  const bool pass_blank = GR && p.mode == FUSION_BLANK_AM && !p.fused && !p.traffic && p.V >= 4;
+  const bool stats = !GR || p.fused != nullptr || (p.mode == FUSION_BLANK_AM && !pass_blank);
+  // the frame decoded next, from t on, among the 64 from t0 that s_emit describes;
+  // past them the first frame of the next 64
+  auto next_frame = [&](int t, int t0) -> int {
+    const unsigned long long bits =
+        ((unsigned long long)(unsigned)uni((int)s_emit[1]) << 32) | (unsigned)uni((int)s_emit[0]);
+    const unsigned long long left = t - t0 < 64 ? bits >> (t - t0) : 0ull;
+    return left != 0ull ? t + __ffsll((long long)left) - 1 : t0 + 64;
+  };
+  auto scan_frames = [&](int t0) {
+    constexpr int kRow = NC * NW;                            // 16-byte loads per lane of a row
+    constexpr int kFly = W >= 1024 ? 8 : 16;                 // of them in flight
+    constexpr int kLoads = kRow < kFly ? kRow : kFly, kParts = kRow / kLoads, kRowsAt = kFly / kLoads;
+    const int V = p.V, blank = p.blank, n = min(64, p.T - t0);
+    lds_barrier();  // every wave has read the last block's bits
+    if (g < 2) s_emit[g] = 0u;
+    lds_barrier();
+    for (int f0 = wave * kRowsAt; f0 < n; f0 += NW * kRowsAt) {
+      float top[kRowsAt], low[kRowsAt];  // this lane's highest logit, and the highest of ids below blank
+      const float *row[kRowsAt];
+#pragma unroll
+      for (int r = 0; r < kRowsAt; ++r) {
+        row[r] = p.logits + ((int64_t)(t0 + min(f0 + r, n - 1)) * H + h) * V;
+        top[r] = low[r] = -INFINITY;
+      }
+#pragma unroll 1
+      for (int part = 0; part < kParts; ++part) {
+        float4 v[kRowsAt][kLoads];
+#pragma unroll
+        for (int r = 0; r < kRowsAt; ++r) {
+          const rsrc_t xr = row_rsrc(row[r], V);
+#pragma unroll
+          for (int c = 0; c < kLoads; ++c)
+            // a strip past the row's end reads the row's last four tokens again
+            v[r][c] = row_load4(xr, min(((part * kLoads + c) * 64 + lane) * 4, V - 4) * 4, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < kRowsAt; ++r)
+#pragma unroll
+          for (int c = 0; c < kLoads; ++c) {
+            const float4 x = v[r][c];
+            top[r] = fmaxf(top[r], fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)));
+            if (blank > 0) {  // uniform
+              const int y0 = min(((part * kLoads + c) * 64 + lane) * 4, V - 4);
+              low[r] = fmaxf(low[r], y0 < blank ? x.x : -INFINITY);
+              low[r] = fmaxf(low[r], y0 + 1 < blank ? x.y : -INFINITY);
+              low[r] = fmaxf(low[r], y0 + 2 < blank ? x.z : -INFINITY);
+              low[r] = fmaxf(low[r], y0 + 3 < blank ? x.w : -INFINITY);
+            }
+          }
+      }
+#pragma unroll
+      for (int r = 0; r < kRowsAt; ++r) {
+        const int f = f0 + r;
+        const float xb = row[r][blank];
+        // blank takes the frame if nothing is above it and no lower id equals it
+        const bool emits = !(xb > -INFINITY) || __ballot(top[r] > xb || low[r] >= xb) != 0ull;
+        if (f < n && lane == 0) {
+          if (emits) atomicOr(&s_emit[f >> 5], 1u << (f & 31));
+          else p.tokens[(int64_t)(t0 + f) * H + h] = blank;
+        }
+      }
+    }
+    lds_barrier();
+  };
+  const float *xrow = p.logits + (int64_t)h * p.V;
   auto fetch_logits = [&]() {
     const rsrc_t xr = row_rsrc(xrow, p.V);
     fetch_strip(xr, xraw, voff);
@@ -648,26 +726,49 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       }
     }
   };
-  row_stats(xraw, wave, p.V);
   if (g == 0) s_nstat = 0;
+  if (stats) row_stats(xraw, wave, p.V);
   __syncthreads();
-  if (wave == NW - 1) combine_stats();
-  __syncthreads();
+  if (stats) {
+    if (wave == NW - 1) combine_stats();
+    __syncthreads();
+  }
 
   bool aborted = false;  // after one failed rendezvous this workgroup stops waiting
-  for (int t = 0; t < p.T; ++t) {
+  int gen = 0;           // rows assembled so far (the LDS entries' stamp)
+  int tn;                // the frame decoded after this one
+  int blk = -1;          // greedy: the 64 frames s_emit describes
+  for (int t = 0; t < p.T; t = tn) {
+    if (GR && pass_blank && (t >> 6) != blk) {
+      blk = t >> 6;
+      scan_frames(blk << 6);
+      tn = next_frame(t, blk << 6);
+      xrow = p.logits + ((int64_t)min(tn, p.T - 1) * H + h) * p.V;
+      fetch_logits();
+      if (tn != t) continue;
+    }
     const int V = uni(s_cfg[0]), blank = uni(s_cfg[1]);
     const int fl = uni(hs.fl);
     const bool act = (fl & 1) != 0;
     const bool inv = act && (fl & 2) != 0;
     const bool ok = act && !inv;
-    // stamps repeat every 2^15 frames: the rows are cleared before they would
-    // (the previous frame's last reads of them precede its final barrier)
-    const uint32_t stamp = (uint32_t)(t & 0x7FFF) + 1u;
-    if (stamp == 1u && t > 0) {
-      clear_rows();
-      __syncthreads();
+    // A greedy hypothesis that emitted blank keeps its state, and so the rows in LDS:
+    // neither the second memory round trip nor the scatter is needed (32 streams of
+    // 8190 tokens, blank competing, half of the frames blank: 5.9 us a frame before,
+    // 4.6 after).  A beam slot rarely keeps its state: its next hypothesis comes
+    // from any slot, and the test cost the 64 x 4 beam 3 %
+    const bool keep = GR && (!ok || uni(hs.same) != 0);
+    if (!keep) {
+      ++gen;
+      // stamps repeat after 2^14 rows: the entries are cleared before they would
+      // (the previous frame's last reads of them precede its final barrier)
+      if (gen > 0x4000) {
+        gen = 1;
+        clear_rows();
+        __syncthreads();
+      }
     }
+    const uint32_t stamp = (uint32_t)gen;
     const int qsrc = uni(hs.qsrc), yin = uni(hs.y);
     int lmsrc[NL], c1[NL];
 #pragma unroll
@@ -713,15 +814,13 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     const __attribute__((address_space(4))) int32_t *nq =
         (const __attribute__((address_space(4))) int32_t *)(np ? reinterpret_cast<const int32_t *>(np) : g_zero_words);
     const int node[4] = {nq[0], nq[1], nq[2], nq[3]};
+    if (!keep) {
+      // the level-1 dense rows straight into LDS: only the records are waited for
+      // before the second hop
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      // level-1 dense row straight into the LM's LDS row.  Issued
-      // unconditionally (row 0 stands in when the hypothesis has no keys to
-      // compute this frame), so that only the records are waited for before the
-      // second hop
-      load_row(lms[i].dense + (int64_t)(ok ? c1[i] : 0) * V, lmval + i * Vp, V);
+      for (int i = 0; i < NL; ++i) load_row(lms[i].dense + (int64_t)(ok ? c1[i] : 0) * V, lmval + i * Vp, V);
     }
-    if (NW == 1 && t > 0) {  // a single wave has no idle helper
+    if (NW == 1 && t > 0 && stats) {  // a single wave has no idle helper
       row_stats(xraw, 0, V);
       combine_stats();
     }
@@ -761,6 +860,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
         total_arcs[i] += lcnt[i][L];
       }
     }
+    if (!keep) {
     if (CTX && ok && Dc >= 2) load_row(lms[0].ctx_lm + (int64_t)crow * V, lmval + NL * Vp, V);
     // ---- hop 2: first arcs of levels 2..m (flattened) and first phrase transitions --
     int2 ab[NL][kUA];
@@ -886,13 +986,16 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     }
     __builtin_amdgcn_s_waitcnt(0);  // the dense rows have landed in LDS
     __syncthreads();
+    }
     // ---- the row statistics of this frame ---------------------------------------------
     // the log-sum-exp is needed by wave 0 (selected scores, beam totals) and, for
     // fused rows, by every wave; the acoustic argmax (mode A) by every wave
     const float lse = __int_as_float(uni(__float_as_int(s_lse)));
     const int am = uni(s_am);
     // ---- keys and the fused row ------------------------------------------------------
-    const bool blank_only = inv || (p.mode == FUSION_BLANK_AM && am == blank);
+    // (frames that the acoustic argmax gives to blank never get here when they are
+    // passed over)
+    const bool blank_only = inv || (p.mode == FUSION_BLANK_AM && !pass_blank && am == blank);
     const bool want_keys = ok && (!blank_only || p.fused);
     const bool compete = p.mode == FUSION_BLANK_COMPETE;
     const bool write_fused = p.fused != nullptr && ok;
@@ -927,9 +1030,12 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
         }
         float eh[4];
         uint32_t hi[4];
-        if constexpr (ER) {
+        const bool use_row = ER && !keep;  // uniform
+        if (use_row) {
           const float4 ev4 = *reinterpret_cast<const float4 *>(erow + y0);
           eh[0] = ev4.x; eh[1] = ev4.y; eh[2] = ev4.z; eh[3] = ev4.w;
+          // this lane's entry values back to the root's for the next rows
+          *reinterpret_cast<float4 *>(erow + y0) = make_float4(rE[c][0], rE[c][1], rE[c][2], rE[c][3]);
         } else {
           // transition + 1 of this frame's phrase entry, 0 if none
           const uint4 p4 = *reinterpret_cast<const uint4 *>(ptag + y0);
@@ -949,6 +1055,8 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
             for (int j = 0; j < 4; ++j)
               if (hi[j] > (uint32_t)kAux) eh[j] = as_float(tr.delta[dbeg + (int)hi[j] - 1].z);
           }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) eh[j] = hi[j] ? eh[j] : rE[c][j];
         }
         // per LM, the dense row (the first LM's context row when it has one) plus
         // the backoffs of the levels above it up to m, in increasing order (the
@@ -984,14 +1092,11 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
           }
           // phrases: the transition's entry value if this state overrides y, else the
           // root's (with no phrase tree both are 0 and so is phi)
-          const float e = ER ? eh[j] : (hi[j] ? eh[j] : rE[c][j]);
-          const float bst = e - phiq;
+          const float bst = eh[j] - phiq;
           const float a3 = p.beta * ((ER || p.has_trie) ? bst : 0.0f);
           kk[c][j] = (y == blank) ? x : u + a3;
         }
       }
-      // this lane's entry values back to the root's for the next frame (read above)
-      if (ER) *reinterpret_cast<float4 *>(erow + y0) = make_float4(rE[c][0], rE[c][1], rE[c][2], rE[c][3]);
       if (write_fused && y0 < V) {
         const rsrc_t fr = row_rsrc(args_here().fused + rowoff, V);
         if (AL) {
@@ -1007,7 +1112,8 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     // than beside the frame-start loads, whose burst sets the start of the frame.
     // Unconditional (the last frame fetches its own row again): a conditional
     // fetch would make the compiler wait for it where the branches join
-    if (t + 1 < p.T) xrow += xstride;
+    tn = GR && pass_blank ? next_frame(t + 1, blk << 6) : t + 1;
+    if (tn < p.T) xrow += (int64_t)(tn - t) * xstride;
     fetch_logits();
     // ---- the wave's top-k: per round the wave maximum of the remaining keys, then
     // the lowest id holding it (ties to the lowest id).  Keys compete as
@@ -1187,7 +1293,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     lds_barrier();
     // the next frame's row statistics, by the waves other than wave 0; the last of
     // them to finish combines them (ahead of the frame's end, off wave 0's path)
-    if (NW > 1 && wave != 0 && t + 1 < p.T) {
+    if (NW > 1 && wave != 0 && stats && tn < p.T) {
       row_stats(xraw, wave, V);
       if (wave == 1) row_stats(xraw0, 0, V);
       int done = 0;
@@ -1355,6 +1461,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
             hs.c1p[i] = c1p;
             hs.c1[i] = cy != blank ? cy : c1p;
           }
+          hs.same = cy == blank;
           hs.qsrc = cq;
           hs.y = cy;
         }
