@@ -1096,6 +1096,10 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
           const float a3 = p.beta * ((ER || p.has_trie) ? bst : 0.0f);
           kk[c][j] = (y == blank) ? x : u + a3;
         }
+      } else if (GR && ER && !keep) {
+        // a frame given to blank without its keys: the overrides it scattered go all
+        // the same (the frames that keep these rows find them through ptag)
+        *reinterpret_cast<float4 *>(erow + y0) = make_float4(rE[c][0], rE[c][1], rE[c][2], rE[c][3]);
       }
       if (write_fused && y0 < V) {
         const rsrc_t fr = row_rsrc(args_here().fused + rowoff, V);

@@ -55,3 +55,28 @@ def test_blank_frames(V, n_lm, mode):
         x[13 % T, 4, (blank + 2) % V] = np.nan
         for a, b in zip(_decode(glms, gtr, x, S, V, blank, mode), _decode(glms, gtr, x, S, V, blank, mode, fused=True)):
             assert np.array_equal(a, b), blank
+
+
+@pytest.mark.parametrize("V", [130, 1001, 2048])
+def test_blank_frames_counted(V):
+    """A run that counts its bytes goes through every frame: one that blank takes
+    leaves nothing of its phrase state to the frames of the next state."""
+    rng = np.random.default_rng(V)
+    S, T = 6, 150
+    lm = tiny_random_lm(rng, V, 3, n_sent=400)
+    ph = tiny_random_phrases(rng, V, n=30, max_len=5, alphabet=8)
+    x = rng.normal(0.0, 1.0, size=(T, S, V)).astype(np.float32)
+    x[:, :, 1:9] += 3.0
+    x[:, :, 0] += np.where(rng.random((T, S)) < 0.5, 9.0, -9.0)
+    ls = torch.full((S,), V, dtype=torch.int32, device="cuda")
+    bs = torch.zeros((S,), dtype=torch.int32, device="cuda")
+    count = torch.zeros(2, dtype=torch.int64, device="cuda")
+    out = F.run(F.ngram_load_arrays(lm), F.boost_build_phrases(V, 0, ph), torch.from_numpy(x).to("cuda"), S, 1, 1, 0.5,
+                2.0, 0, F.FUSION_BLANK_AM, ls, bs, traffic=count)
+    torch.cuda.synchronize()
+    assert F.fusion_device_status() == 0
+    r = oracle.run(oracle.OracleLM(lm), oracle.OracleTrie(V, 0, ph), x, S, 1, 1, 0.5, 2.0, 0, F.FUSION_BLANK_AM,
+                   [V] * S, [0] * S, threads=4)
+    tok = out["tokens"].cpu().numpy()
+    assert np.array_equal(tok, r["tokens"]), np.argwhere(tok != r["tokens"])[:3]
+    assert np.array_equal(bs.cpu().numpy(), r["boost_state"])
