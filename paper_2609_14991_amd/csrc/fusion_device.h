@@ -345,7 +345,6 @@ struct HypState {
   int lmsrc[NL], c1p[NL], c1[NL], cur_lm[NL];
   int qsrc, y, fl;  // phrase source, token; flags 1 alive, 2 invalid
   int cur_q;        // phrase state scored this frame
-  int same;         // greedy: the state of the frame before (blank emitted), whose rows in LDS still hold
   double S;         // running beam score
   unsigned long long hist;  // 48-bit hash of the history (initial states, emitted tokens): recombination
 };
@@ -388,6 +387,10 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   __shared__ int s_am;     // and the lowest id holding its maximum
   __shared__ int s_nstat;  // waves done with the next frame's strip statistics
   __shared__ unsigned s_emit[2];  // greedy: which of 64 frames blank does not take
+  // greedy: each wave's best, (key image, token, first LM's source, phrase source) and the
+  // second LM's source; frames alternate between two buffers
+  __shared__ __align__(16) int4 s_best[2][MODE == kModeGreedy ? kMaxWaves : 1];
+  __shared__ int s_best1[2][MODE == kModeGreedy ? kMaxWaves : 1];
   __shared__ int w_key[kMaxWaves][KM];  // order-preserving images of the keys (ord_key)
   __shared__ int w_y[kMaxWaves][KM];
   // each wave's best key with its wave index, and the hypothesis' listed entries
@@ -436,7 +439,8 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   constexpr bool BEAM = MODE >= kModeBeam;
   constexpr bool RC = RCM;
   constexpr bool WIDE = MODE == kModeBeamWide || MODE == kModeBeamRCWide;  // more than 64 candidates a stream
-  const int B = BEAM ? p.B : 1, K = p.k;
+  constexpr bool GR = MODE == kModeGreedy;
+  const int B = BEAM ? p.B : 1, K = GR ? 1 : p.k;
   int Nl[NL], RSl[NL];  // order and record stride of each LM
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
@@ -517,7 +521,6 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     hs.y = -1;
     hs.fl = (alive ? 1 : 0) | ((ok_lm && ok_q) ? 0 : 2);
     hs.cur_q = q;
-    hs.same = 0;
     hs.S = sc;
     if constexpr (RC) {
       // the history carried from an earlier call, else one that starts at the
@@ -573,7 +576,6 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   // each wave reading whole rows, several in flight.  The row statistics then serve
   // no purpose (a greedy decision compares keys) and are left out too.  285 greedy
   // streams of 63 speech-like frames, half of them blank: 261 us before, 140 after
-  constexpr bool GR = MODE == kModeGreedy;
   const bool pass_blank = GR && p.mode == FUSION_BLANK_AM && !p.fused && !p.traffic && p.V >= 4;
   const bool stats = !GR || p.fused != nullptr || (p.mode == FUSION_BLANK_AM && !pass_blank);
   // the frame decoded next, from t on, among the 64 from t0 that s_emit describes;
@@ -737,6 +739,25 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   bool aborted = false;  // after one failed rendezvous this workgroup stops waiting
   int gen = 0;           // rows assembled so far (the LDS entries' stamp)
   int tn;                // the frame decoded after this one
+  // Greedy: every wave holds the hypothesis state itself, in scalar registers.  Each
+  // wave resolves its own best token's next state while it still may read the LDS
+  // rows, and after one barrier every wave picks the winner among the waves' bests:
+  // no wave-0 phase with the others waiting and no second barrier (64 streams of 500
+  // frames, 1024 tokens: 3.75 us a frame before, 3.3 after; 285 streams of 63: 180 us
+  // before, 158 after; 8190 tokens: no change)
+  int st_src[NL], st_c1p[NL], st_c1[NL], st_q = 0, st_y = 0, st_fl = 0, st_par = 0;
+  bool st_same = false;  // blank was emitted: the state of the frame before, whose rows in LDS still hold
+  if constexpr (GR) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      st_src[i] = uni(hs.lmsrc[i]);
+      st_c1p[i] = uni(hs.c1p[i]);
+      st_c1[i] = uni(hs.c1[i]);
+    }
+    st_q = uni(hs.qsrc);
+    st_y = uni(hs.y);
+    st_fl = uni(hs.fl);
+  }
   int blk = -1;          // greedy: the 64 frames s_emit describes
   for (int t = 0; t < p.T; t = tn) {
     if (GR && pass_blank && (t >> 6) != blk) {
@@ -748,7 +769,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       if (tn != t) continue;
     }
     const int V = uni(s_cfg[0]), blank = uni(s_cfg[1]);
-    const int fl = uni(hs.fl);
+    const int fl = GR ? st_fl : uni(hs.fl);
     const bool act = (fl & 1) != 0;
     const bool inv = act && (fl & 2) != 0;
     const bool ok = act && !inv;
@@ -757,7 +778,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     // 8190 tokens, blank competing, half of the frames blank: 5.9 us a frame before,
     // 4.6 after).  A beam slot rarely keeps its state: its next hypothesis comes
     // from any slot, and the test cost the 64 x 4 beam 3 %
-    const bool keep = GR && (!ok || uni(hs.same) != 0);
+    const bool keep = GR && (!ok || st_same);
     if (!keep) {
       ++gen;
       // stamps repeat after 2^14 rows: the entries are cleared before they would
@@ -769,12 +790,12 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       }
     }
     const uint32_t stamp = (uint32_t)gen;
-    const int qsrc = uni(hs.qsrc), yin = uni(hs.y);
+    const int qsrc = GR ? st_q : uni(hs.qsrc), yin = GR ? st_y : uni(hs.y);
     int lmsrc[NL], c1[NL];
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      lmsrc[i] = uni(hs.lmsrc[i]);
-      c1[i] = uni(hs.c1[i]);
+      lmsrc[i] = GR ? st_src[i] : uni(hs.lmsrc[i]);
+      c1[i] = GR ? st_c1[i] : uni(hs.c1[i]);
     }
     // ---- hop 1: state records, phrase node, dense level-1 rows ------------------
     const int32_t *rp[NL];
@@ -783,7 +804,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       rp[i] = nullptr;
       if (ok) {
         if (lmsrc[i] < -1) rp[i] = lms[i].ctx_rec + ((int64_t)(-lmsrc[i] - 2) * V + yin) * RSl[i];
-        else if (lmsrc[i] < 0) rp[i] = lms[i].rec_dense + ((int64_t)uni(hs.c1p[i]) * V + yin) * RSl[i];
+        else if (lmsrc[i] < 0) rp[i] = lms[i].rec_dense + ((int64_t)(GR ? st_c1p[i] : uni(hs.c1p[i])) * V + yin) * RSl[i];
         else if (lmsrc[i] >= V + 2) rp[i] = lms[i].rec + (int64_t)(lmsrc[i] - V - 2) * RSl[i];
       }
     }
@@ -900,11 +921,13 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       if (j < dcnt) dd[u] = tr.delta[dbeg + j];
     }
     if (ok && g == 0) {
-      hs.cur_q = qid;
+      if (!GR) hs.cur_q = qid;
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
-        hs.cur_lm[i] = sid[i];
-        hs.c1[i] = c1[i];
+        if (!GR) {
+          hs.cur_lm[i] = sid[i];
+          hs.c1[i] = c1[i];
+        }
 #pragma unroll
         for (int L = 2; L < kMaxLevels; ++L) s_lbeg[i][L] = lbeg[i][L];
       }
@@ -1214,7 +1237,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
             for (int j = 0; j < 4; ++j) sk[c][j] = sk[c][j] >= thr ? sk[c][j] : INT_MIN;
         }
       }
-      int rk = INT_MIN, ry = INT_MAX;  // lane r: entry r of the wave's list
+      int rk = INT_MIN, ry = INT_MAX;  // lane r: entry r of the wave's list (greedy: every lane holds the one)
       for (int r = 0; r < (listed ? 0 : K); ++r) {
         int lbc[NC];
         int lb = INT_MIN;
@@ -1244,6 +1267,11 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
             jm = sk[c][0] == M ? 0 : jm;
           }
         const int wy = (wc * W + wave * 64 + src) * 4 + __builtin_amdgcn_readlane(jm, src);
+        if constexpr (GR) {
+          rk = M;
+          ry = wy;
+          break;
+        }
         const int kill = lane == src ? wc * 4 + jm : -1;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -1252,7 +1280,35 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
         rk = lane == r ? M : rk;
         ry = lane == r ? wy : ry;
       }
-      if (!listed && lane < K) {
+      if constexpr (GR) {
+        // the state after this wave's best token (see HypState)
+        int cl[NL], cq = qid;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) cl[i] = sid[i];
+        if (ry != INT_MAX && ry != blank) {  // uniform
+          uint32_t aw[NL];
+#pragma unroll
+          for (int i = 0; i < NL; ++i) aw[i] = (uint32_t)(arcw[i * Vp + ry] >> 32);
+          const uint32_t pw = ptag[ry];
+          const int hi = uni((pw >> 16) == stamp ? (int)(pw & 0xFFFFu) : 0);
+#pragma unroll
+          for (int i = 0; i < NL; ++i) {
+            const int lo = uni((aw[i] >> 16) == stamp ? (int)(aw[i] & 0xFFFFu) : 0);
+            cl[i] = (CTX && i == 0 && Dc >= 2) ? -(crow + 2) : -1;
+            if (lo) {
+              const int L = lo >> 13, jj = lo & 0x1FFF, N = Nl[i];
+              cl[i] = L < N - 1 ? (int)(s_sbase[i][L] + s_lbeg[i][L] + jj)
+                    : jj < kAux ? sTN[i * kAux + jj]
+                                : lms[i].top_next[s_lbeg[i][L] + jj - lms[i].arc_base[N - 1]];
+            }
+          }
+          cq = !p.has_trie ? 0 : hi == 0 ? -1 : hi <= kAux ? sDT[hi - 1] : tr.delta[dbeg + hi - 1].y;
+        }
+        if (lane == 0) {
+          s_best[st_par][wave] = make_int4(rk, ry, cl[0], cq);
+          if constexpr (NL > 1) s_best1[st_par][wave] = cl[1];
+        }
+      } else if (!listed && lane < K) {
         w_key[wave][lane] = rk;
         w_y[wave][lane] = ry;
       }
@@ -1306,6 +1362,50 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
         combine_stats();
         if (lane == 0) s_nstat = 0;
       }
+    }
+    if constexpr (GR) {
+      // ---- greedy: the best of the waves' bests, in every wave ------------------------
+      int4 bw = make_int4(INT_MIN, INT_MAX, 0, 0);
+      int b1 = 0;
+      if (lane < NW) {
+        bw = s_best[st_par][lane];
+        if constexpr (NL > 1) b1 = s_best1[st_par][lane];
+      }
+      const int M = wave_max_i(bw.x);
+      unsigned long long top = __ballot(bw.x == M && lane < NW);
+      if constexpr (NC > 1) {
+        // equal keys: the lowest id, which with several strips per lane may be any wave's
+        if (top & (top - 1)) {
+          const int ym = ~wave_max_i(bw.x == M ? ~bw.y : INT_MIN);
+          top = __ballot(bw.x == M && bw.y == ym && lane < NW);
+        }
+      }
+      const int from = __ffsll((long long)top) - 1;
+      const int cy = __builtin_amdgcn_readlane(bw.y, from);
+      st_q = __builtin_amdgcn_readlane(bw.w, from);
+      st_same = cy == blank;
+      st_y = cy;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        st_src[i] = i == 0 ? __builtin_amdgcn_readlane(bw.z, from) : __builtin_amdgcn_readlane(b1, from);
+        st_c1p[i] = c1[i];
+        st_c1[i] = cy != blank ? cy : c1[i];
+      }
+      st_par ^= 1;
+      if (g == 0) {
+        // for the byte count and the final state
+        p.tokens[(int64_t)t * H + h] = cy;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+          hs.lmsrc[i] = st_src[i];
+          hs.c1p[i] = st_c1p[i];
+          hs.c1[i] = st_c1[i];
+        }
+        hs.qsrc = st_q;
+        hs.y = cy;
+      }
+      if (stats) lds_barrier();  // the next frame's statistics
+      continue;
     }
     // ---- the hypothesis' top-k (wave 0): the K-entry lists of the NW waves spread
     // over the lanes (entry j of wave w is element e = j*NW + w, lane e % 64, slot
@@ -1455,21 +1555,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
             p.next_boost[o] = q;
           }
         }
-      } else if (MODE == kModeGreedy) {
-        if (lane == 0) {
-          p.tokens[(int64_t)t * H + h] = cy;
-#pragma unroll
-          for (int i = 0; i < NL; ++i) {
-            const int c1p = hs.c1[i];
-            hs.lmsrc[i] = cl[i];
-            hs.c1p[i] = c1p;
-            hs.c1[i] = cy != blank ? cy : c1p;
-          }
-          hs.same = cy == blank;
-          hs.qsrc = cq;
-          hs.y = cy;
-        }
-      } else {
+      } else if constexpr (BEAM) {
         // ---- beam: publish this hypothesis' candidates, meet the stream, rank all ----
         // A candidate record is XW = 4 + NL 64-bit words, each carrying the frame
         // tag in its top 16 bits over 48 bits of payload: the total score S_b +
