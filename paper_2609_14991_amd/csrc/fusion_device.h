@@ -552,6 +552,15 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   // logits strip of this lane, raw (masked per frame): frame t+1's strip is
   // fetched during frame t, so it is in registers when t+1 begins
   const int voff = g * 16;
+  // Rows that are not whole 16-byte strips (AL false: V % 4 != 0, or a base off 16
+  // bytes) are read in 16-byte strips all the same, from 4-byte aligned addresses:
+  // four loads a strip kept the address units busy for longer than the memory
+  // (32 greedy streams of 8190
+  // tokens: 584 us for 120 frames before, 540 after; a step of 777 x 1001 with its
+  // fused rows, which leave in strips too: 13.9 and 13.6).  A strip that would pass the row's end reads the row's last four
+  // tokens, and strip_of shifts them into place.  Only the smallest shape, where
+  // rows may be shorter than a strip, reads single tokens
+  constexpr bool SHIFT = !AL && W > 64;
   float xraw[NC][4];
   float xraw0[NC][4];  // wave 1: wave 0's strip too, for its row statistics
   auto fetch_strip = [&](const rsrc_t &xr, float (&dst)[NC][4], int off) {
@@ -560,9 +569,33 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       if (AL) {
         const float4 xx = row_load4(xr, off, c * W * 16);
         dst[c][0] = xx.x; dst[c][1] = xx.y; dst[c][2] = xx.z; dst[c][3] = xx.w;
+      } else if (SHIFT) {
+        const float4 xx = row_load4(xr, min(off + c * W * 16, p.V * 4 - 16), 0);
+        dst[c][0] = xx.x; dst[c][1] = xx.y; dst[c][2] = xx.z; dst[c][3] = xx.w;
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) dst[c][j] = row_load1(xr, off + 4 * j, c * W * 16);
+      }
+    }
+  };
+  // lane's strip c of wave sw's as fetched, its V % 4 last tokens in the row's last strip in place
+  auto strip_of = [&](const float (&xs)[NC][4], int c, int sw, int V, float (&x)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = xs[c][j];
+    if constexpr (SHIFT) {
+      const int r = V & 3, at = (V >> 2) - (c * W + sw * 64);  // the lane holding the row's last strip (uniform)
+      if (r != 0 && at >= 0 && at < 64) {
+        const bool last = lane == at;
+        if (r == 1) {
+          x[0] = last ? x[3] : x[0];
+        } else if (r == 2) {
+          x[0] = last ? x[2] : x[0];
+          x[1] = last ? x[3] : x[1];
+        } else {
+          x[0] = last ? x[1] : x[0];
+          x[1] = last ? x[2] : x[1];
+          x[2] = last ? x[3] : x[2];
+        }
       }
     }
   };
@@ -658,12 +691,14 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     float xv[NC][4];  // tokens >= V: -inf
     float lmx = -INFINITY;
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+    for (int c = 0; c < NC; ++c) {
+      strip_of(xs, c, sw, V, xv[c]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        xv[c][j] = (c * W + sw * 64 + lane) * 4 + j < V ? xs[c][j] : -INFINITY;
+        xv[c][j] = (c * W + sw * 64 + lane) * 4 + j < V ? xv[c][j] : -INFINITY;
         lmx = fmaxf(lmx, xv[c][j]);
       }
+    }
     const float mw = wave_max_f(lmx);
     float lsum = 0.0f;
     if (mw > -INFINITY) {
@@ -716,16 +751,10 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int wbase = c * W + wave * 64;  // first 4-token strip of this wave
-      if (AL) {
-        const int y0 = (wbase + lane) * 4;
-        __builtin_amdgcn_global_load_lds(drow + (y0 < V ? y0 : 0), (lds_ptr_t)(row + wbase * 4), 16, 0, 0);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int y = wbase * 4 + j * 64 + lane;
-          __builtin_amdgcn_global_load_lds(drow + (y < V ? y : 0), (lds_ptr_t)(row + wbase * 4 + j * 64), 4, 0, 0);
-        }
-      }
+      // (of a row that is not whole strips, the last strip reads up to 12 bytes past it:
+      // the next row, or the pad behind the table)
+      const int y0 = (wbase + lane) * 4;
+      __builtin_amdgcn_global_load_lds(drow + (y0 < V ? y0 : 0), (lds_ptr_t)(row + wbase * 4), 16, 0, 0);
     }
   };
   if (g == 0) s_nstat = 0;
@@ -817,9 +846,11 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     for (int c = 0; c < NC; ++c) asm volatile("" ::"v"(xraw[c][0]), "v"(xraw[c][1]), "v"(xraw[c][2]), "v"(xraw[c][3]));
     float xv[NC][4];
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+    for (int c = 0; c < NC; ++c) {
+      strip_of(xraw, c, wave, V, xv[c]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) xv[c][j] = (act && (c * W + g) * 4 + j < V) ? xraw[c][j] : -INFINITY;
+      for (int j = 0; j < 4; ++j) xv[c][j] = (act && (c * W + g) * 4 + j < V) ? xv[c][j] : -INFINITY;
+    }
     // the state records and the phrase node with scalar loads (uniform addresses):
     // kRecW words per record (the record arrays carry a tail pad so that reading
     // past a short record stays inside them); "no record" / "no node" read the
@@ -1126,7 +1157,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       }
       if (write_fused && y0 < V) {
         const rsrc_t fr = row_rsrc(args_here().fused + rowoff, V);
-        if (AL) {
+        if (AL || y0 + 3 < V) {
           row_store4(fr, make_float4(kk[c][0] - lse, kk[c][1] - lse, kk[c][2] - lse, kk[c][3] - lse), voff, c * W * 16);
         } else {
 #pragma unroll

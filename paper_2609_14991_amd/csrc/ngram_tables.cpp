@@ -16,7 +16,8 @@ struct DeviceUpload {
   NgramTables *t;
   hipStream_t stream;
   // pad: zeroed bytes after the data (the kernels read state records with
-  // fixed-size scalar loads that may run past the last record)
+  // fixed-size scalar loads that may run past the last record, and rows of V
+  // tokens in strips of four)
   template <class T, class D>
   int put(const std::vector<T> &h, const D **dst, size_t pad = 0) {
     static_assert(sizeof(T) == sizeof(D), "host and device element sizes differ");
@@ -42,6 +43,8 @@ struct DeviceUpload {
 
 // the kernels read kRecW = 16 words from the start of any record
 constexpr size_t kRecordPad = 64;
+// and V-wide rows in 16-byte strips
+constexpr size_t kRowPad = 16;
 
 }  // namespace
 
@@ -73,14 +76,14 @@ extern "C" int ngram_load(int32_t order, int32_t vocab, int32_t blank_id, const 
   std::memcpy(d.arc_base, h.arc_base, sizeof d.arc_base);
   std::memcpy(t->n, h.n, sizeof t->n);
   DeviceUpload up{t, stream};
-  if (rc == FUSION_OK) rc = up.put(h.dense, &d.dense);
+  if (rc == FUSION_OK) rc = up.put(h.dense, &d.dense, kRowPad);
   if (rc == FUSION_OK) rc = up.put(h.rec_dense, &d.rec_dense, kRecordPad);
   if (rc == FUSION_OK) rc = up.put(h.cnt1, &d.cnt1);
   if (rc == FUSION_OK) rc = up.put(h.eos1, &d.eos1);
   if (rc == FUSION_OK) rc = up.put(h.rec, &d.rec, kRecordPad);
   if (rc == FUSION_OK) rc = up.put(h.arcs, &d.arcs);
   if (rc == FUSION_OK) rc = up.put(h.top_next, &d.top_next);
-  if (rc == FUSION_OK) rc = up.put(h.ctx_lm, &d.ctx_lm);
+  if (rc == FUSION_OK) rc = up.put(h.ctx_lm, &d.ctx_lm, kRowPad);
   if (rc == FUSION_OK) rc = up.put(h.ctx_rec, &d.ctx_rec, kRecordPad);
   if (rc == FUSION_OK) {
     hipError_t e = hipStreamSynchronize(stream);

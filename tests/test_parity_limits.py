@@ -63,6 +63,31 @@ def test_step_large_vocab(V):
         assert np.abs(g["scores"].cpu().numpy().astype(np.float64) - r["scores"]).max() <= SCORE_TOL
 
 
+@pytest.mark.parametrize("V", [257, 258, 259, 510, 1021, 1022, 1023, 1026, 1539, 4093, 4094, 4095, 4098, 4099, 8189])
+def test_step_partial_strip(V):
+    """Rows whose last 4-token strip holds 1, 2 or 3 tokens, in its first, middle and last lanes."""
+    test_step_large_vocab(V)
+
+
+@pytest.mark.parametrize("V", [256, 260, 1024, 4096, 8188])
+def test_run_rows_off_16_bytes(V):
+    """Whole strips from a base that is only 4-byte aligned: the aligned decode's tokens."""
+    rng, lm, ph = models(V, V)
+    glm, gtr = F.ngram_load_arrays(lm), F.boost_build_phrases(V, 0, ph)
+    S, T = 3, 20
+    x = torch.from_numpy((rng.standard_normal((T, S, V)) * 2).astype(np.float32)).to(dev())
+    off = torch.zeros(x.numel() + 1, device=dev())[1:].view(T, S, V).copy_(x)
+    got = []
+    for a in (x, off):
+        ls = torch.full((S,), V, dtype=torch.int32, device=dev())
+        bs = torch.zeros((S,), dtype=torch.int32, device=dev())
+        out = F.run(glm, gtr, a, S, 1, 1, 0.5, 0.5, 0, F.FUSION_BLANK_COMPETE, ls, bs, want_fused=True)
+        torch.cuda.synchronize()
+        got.append([out["tokens"].cpu().numpy(), out["fused"].cpu().numpy(), ls.cpu().numpy(), bs.cpu().numpy()])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 def _beam_vs_oracle(V, S, B, k, T, seed):
     rng, lm, ph = models(V, seed)
     glm, gtr = F.ngram_load_arrays(lm), F.boost_build_phrases(V, 0, ph)
