@@ -393,9 +393,9 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   __shared__ int s_best1[2][MODE == kModeGreedy ? kMaxWaves : 1];
   __shared__ int w_key[kMaxWaves][KM];  // order-preserving images of the keys (ord_key)
   __shared__ int w_y[kMaxWaves][KM];
-  // each wave's best key with its wave index, and the hypothesis' listed entries
+  // the best keys of 16 groups of lanes, and the hypothesis' listed entries
   // (compacted) and top K, all as sel_order composites (KM > 1)
-  __shared__ __align__(16) int s_wmax[kMaxWaves];
+  __shared__ __align__(16) int s_wmax[16];
   __shared__ __align__(16) unsigned long long s_sel[16];
   __shared__ unsigned long long s_win[KM];
   __shared__ HypState<NL> hs;
@@ -1191,9 +1191,12 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
           sk[c][j] = cd[c][j] ? o : INT_MIN;
         }
       // With K > 1 the rounds below run only in a wave that holds more than K
-      // keys at or above tau, the K-th largest of the NW wave maxima: those
-      // maxima are K distinct tokens with keys >= tau, so no key below tau is
-      // among the hypothesis' top K.  A wave with at most K such keys writes
+      // keys at or above tau, the K-th largest of 16 maxima, one of every 64, 16 or
+      // 4 lanes (1024, 256, 64 lanes): those maxima are K distinct tokens with keys
+      // >= tau, so no key below tau is among the hypothesis' top K.  (With one
+      // maximum per wave the bound of a 256-lane hypothesis was the lowest of four
+      // maxima, and there was none for k = 8:
+      // a step of 777 x 1001 with k = 8 took 13.6 us, 12.2 so.)  A wave with at most K such keys writes
       // them straight into its list (any order: the hypothesis' top-k ranks
       // by key, then id).
       bool listed = false;
@@ -1201,35 +1204,34 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
         int lb = INT_MIN;
 #pragma unroll
         for (int c = 0; c < NC; ++c) lb = max(lb, max(max(sk[c][0], sk[c][1]), max(sk[c][2], sk[c][3])));
-        const int mw = wave_max_i(lb);
-        // (the wave index in the low bits makes the maxima distinct; tau, with them
-        // cleared, can only be lower, which keeps it a valid bound)
-        if (lane == 0) s_wmax[wave] = (mw & ~15) | (15 - wave);
-        lds_barrier();
-        int tau = INT_MIN;
-        if (NW >= K) {
-          // the K-th largest of the NW maxima: lane l < NW counts those ahead of
-          // maximum l and the lane of rank K-1 holds it
-          const int mine = s_wmax[lane & (NW - 1)];
-          int wm[kMaxWaves];
-#pragma unroll
-          for (int w2 = 0; w2 < NW; w2 += (NW >= 4 ? 4 : 1)) {
-            if constexpr (NW >= 4) {
-              const int4 d = *reinterpret_cast<const int4 *>(&s_wmax[w2]);
-              wm[w2] = d.x;
-              wm[w2 + 1] = d.y;
-              wm[w2 + 2] = d.z;
-              wm[w2 + 3] = d.w;
-            } else {
-              wm[w2] = s_wmax[w2];
-            }
+        int mw = lb, group = wave;
+        if constexpr (NW == 16) {
+          mw = wave_max_i(mw);
+        } else {
+          static_assert(NW == 4 || NW == 1, "16 groups of lanes");
+          mw = max(mw, dpp_i<0xB1, 0xF>(mw));
+          mw = max(mw, dpp_i<0x4E, 0xF>(mw));
+          if (NW == 4) {
+            mw = max(mw, dpp_i<0x141, 0xF>(mw));
+            mw = max(mw, dpp_i<0x140, 0xF>(mw));
           }
-          int r = 0;
-#pragma unroll
-          for (int w2 = 0; w2 < NW; ++w2) r += (int)(wm[w2] > mine);
-          const unsigned long long at = __ballot(lane < NW && r == K - 1);
-          tau = __builtin_amdgcn_readlane(mine, __ffsll((long long)at) - 1) & ~15;
+          group = g / (W / 16);
         }
+        // (the group in the low bits makes the maxima distinct; tau, with them
+        // cleared, can only be lower, which keeps it a valid bound)
+        if (lane % (W / 16 < 64 ? W / 16 : 64) == 0) s_wmax[group] = (mw & ~15) | (15 - group);
+        lds_barrier();
+        // the K-th largest: lane l < 16 counts those ahead of maximum l and the lane
+        // of rank K-1 holds it
+        const int mine = s_wmax[lane & 15];
+        int r = 0;
+#pragma unroll
+        for (int w2 = 0; w2 < 16; w2 += 4) {
+          const int4 d = *reinterpret_cast<const int4 *>(&s_wmax[w2]);
+          r += (int)(d.x > mine) + (int)(d.y > mine) + (int)(d.z > mine) + (int)(d.w > mine);
+        }
+        const unsigned long long at = __ballot(lane < 16 && r == K - 1);
+        const int tau = __builtin_amdgcn_readlane(mine, __ffsll((long long)at) - 1) & ~15;
         // survivors: keys >= tau, never a non-candidate (INT_MIN; every real key,
         // -inf included, maps above it)
         const int thr = max(tau, INT_MIN + 1);
