@@ -190,7 +190,9 @@ int fusion_step(const NgramTables *lm, const BoostTrie *trie, const float *logit
  *   lm_state, boost_state  device [H], in: initial states, out: final states
  *   hyp_score    device [H] fp64, in/out running scores (B > 1); start a
  *                stream with {0, -inf, ...} for a single live hypothesis
- *   tokens       device [T, H]: token chosen for each slot at each frame
+ *   tokens       device [T, H]: token chosen for each slot at each frame (greedy:
+ *                blank, the state unchanged, where every competing key is the
+ *                all-ones NaN, as in a row of 0xFF bytes)
  *   parents      device [T, H] (B > 1): slot of the previous frame it extends
  *   fused        device [T, H, V] fp32 or NULL (slots of dead hypotheses untouched)
  *   traffic      device [2] int64 or NULL: adds the algorithmic bytes of the

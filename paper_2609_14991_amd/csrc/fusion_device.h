@@ -1250,7 +1250,8 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
     // ---- the wave's top-k: per round the wave maximum of the remaining keys, then
     // the lowest id holding it (ties to the lowest id).  Keys compete as
     // order-preserving ints; tokens that are not candidates or are already taken
-    // hold INT_MIN, below every key including -inf.  The per-round work stays in
+    // hold INT_MIN, below every key including -inf (a key that is the all-ones NaN
+    // maps there too: such a token is no candidate).  The per-round work stays in
     // the vector units (the scalar unit is shared by all the waves of the CU):
     // each lane finds its own first token holding the maximum, the compare mask
     // is the ballot, the winning lane removes its token, and lane r keeps round
@@ -1493,7 +1494,10 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
         }
       }
       const int from = __ffsll((long long)top) - 1;
-      const int cy = __builtin_amdgcn_readlane(bw.y, from);
+      // (every competing key the all-ones NaN, as in a row of 0xFF bytes: no wave has a
+      // candidate, each left the state as it is, and the frame goes to blank)
+      const int yw = __builtin_amdgcn_readlane(bw.y, from);
+      const int cy = yw != INT_MAX ? yw : blank;
       st_q = __builtin_amdgcn_readlane(bw.w, from);
       st_same = cy == blank;
       st_y = cy;

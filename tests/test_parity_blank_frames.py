@@ -80,3 +80,29 @@ def test_blank_frames_counted(V):
     tok = out["tokens"].cpu().numpy()
     assert np.array_equal(tok, r["tokens"]), np.argwhere(tok != r["tokens"])[:3]
     assert np.array_equal(bs.cpu().numpy(), r["boost_state"])
+
+
+@pytest.mark.parametrize("V,n_lm", [(3, 1), (130, 2), (1001, 1), (2048, 1), (8190, 1)])
+@pytest.mark.parametrize("mode", [F.FUSION_BLANK_AM, F.FUSION_BLANK_COMPETE])
+@pytest.mark.parametrize("fused", [False, True])
+def test_rows_of_ff_bytes(V, n_lm, mode, fused):
+    """A row of 0xFF bytes (the all-ones NaN in every token) offers no candidate: the
+    frame goes to blank and the state stays, as if blank had won it outright."""
+    rng = np.random.default_rng(V + mode)
+    blank, S, T = 1, 3, 70
+    lms = [tiny_random_lm(rng, V, 3, n_sent=400, blank=blank) for _ in range(n_lm)]
+    ph = tiny_random_phrases(rng, V, n=12, max_len=3, blank=blank, alphabet=min(V - 1, 12))
+    glms, gtr = [F.ngram_load_arrays(m) for m in lms], F.boost_build_phrases(V, blank, ph)
+    x = rng.normal(0.0, 1.0, size=(T, S, V)).astype(np.float32)
+    x[:, :, blank] += np.where(rng.random((T, S)) < 0.3, 9.0, -9.0)
+    same = x.copy()
+    for t, s in [(0, 0), (5, 1), (6, 1), (64, 2), (T - 1, 0)]:
+        x.view(np.uint32)[t, s] = 0xFFFFFFFF
+        same[t, s] = -50.0
+        same[t, s, blank] = 50.0
+    tok, ls, bs = _decode(glms, gtr, x, S, V, blank, mode, fused=fused)
+    r = oracle.run_lms([oracle.OracleLM(m) for m in lms], [0.5, 0.25][:n_lm], oracle.OracleTrie(V, blank, ph), same, S,
+                       1, 1, 0.5, blank, mode, [[V] * S] * n_lm, [0] * S, threads=4)
+    assert np.array_equal(tok, r["tokens"]), np.argwhere(tok != r["tokens"])[:3]
+    assert np.array_equal(ls, np.asarray(r["lm_state"]).reshape(n_lm, S))
+    assert np.array_equal(bs, r["boost_state"])
