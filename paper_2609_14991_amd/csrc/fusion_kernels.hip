@@ -204,13 +204,18 @@ int launch(Params &p, int n_hyp, hipStream_t stream, unsigned long long *fixed =
   // stream, then the 8 arrival counters (4 words)
   const size_t stream_words = (size_t)2 * p.B * p.k * (3 + p.n_lm + (p.recombine ? 1 : 0));
   constexpr size_t kTicketWords = 4;
-  // Streams are dealt over the 8 blockIdx classes, i.e. XCDs, whatever their
-  // number: a class short of a stream has B workgroups that exit at once.  An
+  // 8 or more streams are dealt over the 8 blockIdx classes, i.e. XCDs, whatever
+  // their number: a class short of a stream has B workgroups that exit at once.  An
   // XCD must then hold its share of the streams.  (Rounding a launch down to
   // whole multiples of 8 streams split 23 streams of 8 slots, two LMs, 2,500
   // tokens into launches of 16 and 7: 2.20 ms instead of 1.13 ms for 60
-  // frames.  Fewer than 8 streams, spread over the XCDs without the classes,
-  // met across XCDs.)
+  // frames.)  Fewer streams are spread over the whole device: by class, a single
+  // stream would always be XCD 0's, several calls at once would share that XCD
+  // while the others idle, and n calls of B slots whose incomplete streams fill it
+  // (n (B - 1) of its slots) would hold each other off until the rendezvous
+  // times out.  Spread, such calls have the device's room.  Measured over 60
+  // frames, 1 to 7 streams: 2 to 4 slots 0-4 % slower spread, 8 slots -2 to 4 %, 16
+  // slots 1-5 % faster.
   const long per_xcd = resident / 8;
   const bool by_xcd = per_xcd >= p.B;
   int s_batch = (int)std::min<long>(p.S, by_xcd ? 8 * (per_xcd / p.B) : resident / p.B);
@@ -247,8 +252,8 @@ int launch(Params &p, int n_hyp, hipStream_t stream, unsigned long long *fixed =
     Params q = p;
     q.s_off = s0;
     q.n_str = ns;
-    q.xcd_map = by_xcd ? 1 : 0;
-    hipLaunchKernelGGL(fn, dim3((by_xcd ? (ns + 7) / 8 * 8 : ns) * p.B), dim3(sh.W), dyn, stream, q);
+    q.xcd_map = by_xcd && ns >= 8 ? 1 : 0;
+    hipLaunchKernelGGL(fn, dim3((q.xcd_map ? (ns + 7) / 8 * 8 : ns) * p.B), dim3(sh.W), dyn, stream, q);
     e = hipGetLastError();
     if (e != hipSuccess) rc = hip_error(e, "fusion kernel launch");
   }
