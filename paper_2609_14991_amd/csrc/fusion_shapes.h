@@ -18,8 +18,8 @@ struct Params {
   int32_t *parents;
   float *fused;
   int64_t *traffic;
-  float *scores;  // fusion_step outputs [H, k]
-  int32_t *next_lm;
+  float *scores;  // fusion_step outputs [H, k]; a one-frame greedy call has no scores (NULL) and
+  int32_t *next_lm;     // its states in place (next_boost NULL without a phrase tree)
   int32_t *next_boost;
   unsigned long long *xchg;  // beam exchange [S][2][B][k] candidate records of four tagged words
   unsigned long long *hist;  // recombination: [H] in/out history hashes (0: derive from the initial states) or NULL
