@@ -139,3 +139,13 @@ def test_several_lm_calls_reject_bad_arguments(lib):
                             None, 1, 1, 1, 4, 1, 0.5, 0, 0, None, None, None, None, None, None, None,
                             0, None, None)
     assert rc == F.FUSION_E_ARG and "NULL" in F.fusion_last_error()
+
+
+@pytest.mark.gpu
+def test_calls_follow_the_current_stream():
+    import torch
+
+    for s in (torch.cuda.default_stream(), torch.cuda.Stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(s):
+            assert (F._stream(None).value or 0) == s.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert (F._stream(None).value or 0) == torch.cuda.current_stream().cuda_stream
