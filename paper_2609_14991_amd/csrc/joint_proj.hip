@@ -33,6 +33,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 64;                       // K per stage
+constexpr int kMapNone = 0, kMap4x2 = 1, kMapRuns = 2;  // tiles to XCDs
 constexpr uint32_t kOutside = 0x80000000u;    // an offset past every descriptor (operands are under 2 GiB)
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes) {
@@ -55,7 +56,7 @@ template <int kWM, int kWN, int kTM, int kTN, int kNB, int kAux>
 __global__ void __launch_bounds__(64 * kWM * kWN, 2) joint_proj_kernel(const uint16_t *__restrict__ A,
                                                                         const uint16_t *__restrict__ W,
                                                                         const float *__restrict__ bias, int M, int N,
-                                                                        int K, int n_col_tiles, int xcd_map,
+                                                                        int K, int n_col_tiles, int map,
                                                                         float *__restrict__ out) {
   constexpr int kRM = 16 * kTM, kRN = 16 * kTN;  // rows and columns of a wave's tile
   constexpr int kBM = kRM * kWM, kBN = kRN * kWN, kWaves = kWM * kWN;
@@ -69,20 +70,28 @@ __global__ void __launch_bounds__(64 * kWM * kWN, 2) joint_proj_kernel(const uin
   __shared__ __align__(1024) unsigned char smem[kNB * kStage];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // tile of this workgroup.  With xcd_map (row tiles a multiple of 4, column
-  // tiles even) workgroup w runs on XCD w % 8 under the hardware's round-robin,
-  // and XCD x takes the row tiles = x % 4 (mod 4) against column half x / 4: a
-  // row band of A is fetched by two XCDs instead of eight and each XCD's L2
-  // keeps half of W.  Otherwise tiles go column-fastest.
+  // tile of this workgroup, which runs on XCD x = blockIdx % 8 under the hardware's
+  // round-robin (see joint_project for the choice):
+  // kMap4x2 (row tiles a multiple of 4, column tiles even): XCD x takes the row
+  // tiles = x % 4 (mod 4) against column half x / 4, so a row band of A is fetched by
+  // two XCDs instead of eight and each XCD's L2 keeps half of W.
+  // kMapRuns: each XCD takes a run of consecutive tiles, column-fastest, so that a row
+  // band of A is fetched by one XCD (two at a run's end) and every L2 holds W.
+  // kMapNone: column-fastest over all XCDs
   int tr, tc;
-  if (xcd_map) {
+  if (map == kMap4x2) {
     const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
     const int half = n_col_tiles >> 1;
     tr = (i / half) * 4 + (x & 3);
     tc = (x >> 2) * half + i % half;
   } else {
-    tr = blockIdx.x / n_col_tiles;
-    tc = blockIdx.x % n_col_tiles;
+    int t = blockIdx.x;
+    if (map == kMapRuns) {
+      const int x = t & 7, per = gridDim.x >> 3, more = gridDim.x & 7;  // the first `more` XCDs take one tile more
+      t = x * per + min(x, more) + (t >> 3);
+    }
+    tr = t / n_col_tiles;
+    tc = t % n_col_tiles;
   }
   const int bn = tc * kBN, bm = tr * kBM;
   const int wm = (wave / kWN) * kRM, wn = (wave % kWN) * kRN;
@@ -216,6 +225,13 @@ extern "C" int joint_project(const uint16_t *A, const uint16_t *W, const float *
   if (M == 0) return FUSION_OK;
   if (!A || !W || !out) return set_error(FUSION_E_ARG, "NULL operand");
   if (((uintptr_t)A | (uintptr_t)W) % 16 != 0) return set_error(FUSION_E_ARG, "A and W must be 16-byte aligned");
+  constexpr ProjCfg<2, 4, 8, 4, 2> t256{};
+  constexpr ProjCfg<2, 2, 4, 4, 2> t128{};
+  constexpr ProjCfg<2, 2, 2, 4, 2> t64x128_3a_cu{};
+  constexpr ProjCfg<2, 2, 2, 4, 3> t64x128{};
+  constexpr ProjCfg<2, 2, 2, 2, 4> t64{};
+  constexpr ProjCfg<2, 2, 1, 2, 4> t32{};
+  constexpr int64_t kCus = 256;
   auto tiles = [&](auto cfg) -> int64_t {
     using C = decltype(cfg);
     return (int64_t)((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
@@ -224,40 +240,66 @@ extern "C" int joint_project(const uint16_t *A, const uint16_t *W, const float *
     using C = decltype(cfg);
     const int nct = (N + C::BN - 1) / C::BN, nrt = (M + C::BM - 1) / C::BM;
     if (tiles(cfg) > 0x7FFFFFFFll) return set_error(FUSION_E_UNSUPPORTED, "too many tiles");
-    const int xcd_map = (nrt % 4 == 0 && nct % 2 == 0) ? 1 : 0;
-    // Rows of whole 128-byte lines leave as streaming stores (nt with sc1: 472 us
-    // for 76800 x 4096 x 640, plain 553); rows that share lines with their
+    // Tiles to XCDs: 4 x 2 where the tiles divide so; else, in a launch of more than a
+    // round, in runs if W fits an L2 (up to 4 MB), has at most 32 column tiles and is
+    // the smaller operand.  Not dealt at all, 128 x 128 tiles fetch every row band of A on
+    // all eight XCDs: 30343 x 1024 x 248 45 us, in runs 36; 48340 x 1024 x 768 117 and 88;
+    // over 190 random sizes that the rule takes 5 % (M < 2 N) to 14 % (M > 8 N) faster in
+    // runs, 256 x 256 tiles 4 to 5 %.  Against 4 x 2 runs gain 7 % to lose 19 %.
+    const bool by4x2 = nrt % 4 == 0 && nct % 2 == 0;
+    const bool runs = tiles(t128) > kCus && M >= N && nct <= 32 && (int64_t)N * K * 2 <= 4 << 20;
+    const int map = by4x2 ? kMap4x2 : runs ? kMapRuns : kMapNone;
+    // Rows of whole 128-byte lines leave as streaming stores (nt with sc1: 459 us
+    // for 76800 x 4096 x 640, plain 535, launches back to back); rows that share lines with their
     // neighbours are left for the L2 to merge (76800 x 1001 x 136: 91 us plain,
     // over 100 streaming)
     const dim3 grid(nct * nrt), block(64 * C::WM * C::WN);
     if (N % 32 == 0)
       hipLaunchKernelGGL((joint_proj_kernel<C::WM, C::WN, C::TM, C::TN, C::NB, 18>), grid, block, 0, stream, A, W, bias,
-                         M, N, K, nct, xcd_map, out);
+                         M, N, K, nct, map, out);
     else
       hipLaunchKernelGGL((joint_proj_kernel<C::WM, C::WN, C::TM, C::TN, C::NB, 0>), grid, block, 0, stream, A, W, bias,
-                         M, N, K, nct, xcd_map, out);
+                         M, N, K, nct, map, out);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? FUSION_OK : hip_error(e, "joint projection launch");
   };
-  // The largest tile that still gives every one of the 256 CUs work: a larger
-  // tile reads less LDS per multiply-accumulate, a smaller one fills the chip.
-  // Measured (us; tiles in brackets):
+  // By the number of tiles, which decides how evenly a launch fills the 256 CUs: a
+  // larger tile reads less LDS per multiply-accumulate, a smaller one fills the
+  // chip.  Measured (us; tiles in brackets):
   //              256x256      128x128      64x128       64x64        32x64
   //   256x4096   19 [16]      9.6 [64]     7.5 [128]    6.2 [256]    6.1 [512]     K = 640
   //   777x2500   12 [40]      7.2 [140]    6.7 [260]    7.8 [520]    7.3 [1000]    K = 256
   //   1664x4096  21 [112]     13.3 [416]   16.7 [832]   20 [1664]    23 [3328]     K = 640
   //   3328x1001  13 [52]      8.3 [208]    7.4 [416]    8.6 [832]    9.2 [1664]    K = 136
-  // 256 x 256 pays from about a thousand tiles and at short K, where a larger
-  // share of the time goes to the epilogue: 76800 x 4096 x 640 472 us against 489,
-  // 25600 x 2500 x 256 63 against 71, but 12800 x 8190 x 1024 260 against 235.
-  constexpr ProjCfg<2, 4, 8, 4, 2> t256{};
-  constexpr ProjCfg<2, 2, 4, 4, 2> t128{};
-  constexpr ProjCfg<2, 2, 2, 4, 3> t64x128{};
-  constexpr ProjCfg<2, 2, 2, 2, 4> t64{};
-  constexpr ProjCfg<2, 2, 1, 2, 4> t32{};
-  constexpr int64_t kCus = 256;
-  if (tiles(t256) >= 1000 && K <= 640) return go(t256);
-  if (tiles(t128) > kCus) return go(t128);
+  // 256 x 256 from a thousand tiles on, except where
+  //   - half of each tile or more would lie past N: 512000 x 100 x 128 took 93 us
+  //     with it, 69 with 128 x 128; x 64 x 640 188 and 151; x 200 x 640 237 and 300
+  //   - K is over 640 and rows are whole lines, for fewer than 2000 tiles, where the two
+  //     are level or 128 x 128 ahead (25600 x 4096: 191 and 177 at K = 704, 218 and 206
+  //     at 832, 249 and 252 at 1024).  With more tiles: 76800 x 4096 508 and 545 us at
+  //     704, 660 and 764 at 1024; 51200 x 4096 341 and 351, 456 and 498; 512000 x 256
+  //     263 and 315, 347 and 397.  With rows that share lines, 1000 tiles do:
+  //     25600 x 2500 117 and 136 at 704, 148 and 169 at 1024
+  // and from 400 on where W is over 4 MB and 128 x 128 tiles cannot be dealt 4 x 2 (A
+  // then goes to all XCDs, half as often): 7711 x 3968 x 648 59 us and 73, 8837 x 6784 x
+  // 504 96 and 118, but 12594 x 4032 x 536 97 and 91.
+  // A single column of them (N of 129 to 256) also pays as one full round, 129 to 256
+  // tiles, and from 400 on: A is read once, not twice (61385 x 208 x 240 18.3 us and
+  // 25.5, in runs 20.4; 188 tiles of 192 x 912 31 and 48, 35; 503 of 181 x 600 62 and 87,
+  // 70; but 299 of 165 x 128 32 and 26).
+  // 128 x 128 holds two workgroups a CU: 513 to 640 tiles of it leave a second
+  // round nearly empty, and 64 x 128 with two stages in LDS (three a CU) is ahead:
+  // 3323 x 2500 x 256 13.3 us and 17.0, 8315 x 1001 x 512 23.1 and 27.7, 3195 x 3072 x
+  // 512 17.1 and 20.4; at 680 tiles the two are level.  Not for wide rows dealt 4 x 2
+  // (2555 x 4096 x 640 24 and 22.8 us) or of a long K (1580 x 5635 x 560 33.8 and 31.1).
+  const int64_t n256 = tiles(t256), n128 = tiles(t128);
+  const bool even128 = (N + 127) / 128 % 2 == 0;
+  const bool t128_4x2 = (M + 127) / 128 % 4 == 0 && even128, t64x128_4x2 = (M + 63) / 64 % 4 == 0 && even128;
+  if (n256 >= 1000 && N > 128 && (K <= 640 || n256 >= 2000 || N % 32 != 0)) return go(t256);
+  if (n256 >= 400 && (int64_t)N * K * 2 > 4 << 20 && !t128_4x2) return go(t256);
+  if (N > 128 && N <= 256 && n256 > kCus / 2 && (n256 <= kCus || n256 >= 400)) return go(t256);
+  if (n128 > 2 * kCus && n128 <= 5 * kCus / 2 && (N < 4096 || (!t64x128_4x2 && K <= 512))) return go(t64x128_3a_cu);
+  if (n128 > kCus) return go(t128);
   // (the narrower tiles store 8 rows at once: their offsets need 8 rows under 2 GiB)
   if (tiles(t64x128) > kCus || N >= (1 << 25)) return go(t64x128);
   if (tiles(t64) > kCus) return go(t64);

@@ -125,7 +125,14 @@ def test_projection_ragged_shapes(M, N, K):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [(31, 4099, 72), (1100, 1030, 200), (2100, 1001, 136), (2200, 2050, 328),
-                                   (33001, 2050, 72), (32768, 2048, 640)])
+                                   (33001, 2050, 72), (32768, 2048, 640),
+                                   # either side of 512 and 640 tiles of 128 x 128, and of the rules for 256 x 256
+                                   (16384, 512, 72), (8193, 1001, 200), (2500, 4160, 136), (20480, 512, 72),
+                                   (10241, 1024, 72), (256001, 100, 72), (256001, 129, 72), (32001, 2050, 648),
+                                   (65600, 2048, 704), (32768, 2048, 648), (8100, 3968, 584),
+                                   (32769, 200, 72), (65537, 200, 72), (102400, 200, 72),
+                                   # tiles dealt in runs, whole and ragged shares of the XCDs
+                                   (4200, 1024, 72), (9000, 130, 136), (5000, 4096, 512)])
 def test_projection_every_tile_shape(M, N, K):
     """One size per tile shape of the dispatch, from 32 x 64 to 256 x 256, with ragged
     rows, columns and last K stages (and one whole-tile size); sampled rows where large."""
