@@ -135,31 +135,80 @@ def test_c2_stream_in_13_frame_chunks(c2):
     assert int(ls.cpu()[0]) == r["lm_state"][0] and int(bs.cpu()[0]) == r["boost_state"][0]
 
 
-def test_long_run_past_the_lds_stamp_period():
-    """One launch of 33068 frames: the LDS rows of explicit arcs and phrase
-    transitions carry a frame stamp that repeats every 32768 frames, so the run
-    crosses the point where they are cleared; every token and the final states
-    equal the oracle's."""
-    rng = np.random.default_rng(91)
-    V, S, T = 300, 2, 32768 + 300
+STAMPS = 16384  # rows assembled between two clears of the LDS entries
+
+
+def _long_run(mode, T, blank_bias, seed):
+    rng = np.random.default_rng(seed)
+    V, S = 300, 2
     lm = tiny_random_lm(rng, V, 4, n_sent=2000)
     ph = tiny_random_phrases(rng, V, n=30, max_len=4, alphabet=20, with_completion=True)
     glm, gtr = F.ngram_load_arrays(lm), F.boost_build_phrases(V, 0, ph)
     olm, otr = oracle.OracleLM(lm), oracle.OracleTrie(V, 0, ph)
     x = (rng.standard_normal((T, S, V)) * 2).astype(np.float32)
-    x[:, :, 0] += 2
+    x[:, :, 0] += blank_bias
     ls = torch.full((S,), V, dtype=torch.int32, device=dev())
     bs = torch.zeros((S,), dtype=torch.int32, device=dev())
-    out = F.run(glm, gtr, torch.from_numpy(x).to(dev()), S, 1, 1, 0.5, 0.5, 0, F.FUSION_BLANK_AM, ls, bs)
+    out = F.run(glm, gtr, torch.from_numpy(x).to(dev()), S, 1, 1, 0.5, 0.5, 0, mode, ls, bs)
     torch.cuda.synchronize()
     assert F.fusion_device_status() == 0
-    r = oracle.run(olm, otr, x, S, 1, 1, 0.5, 0.5, 0, 0, [V] * S, [0] * S, threads=2)
+    r = oracle.run(olm, otr, x, S, 1, 1, 0.5, 0.5, 0, mode, [V] * S, [0] * S, threads=2)
     tok = out["tokens"].cpu().numpy()
-    assert (tok[32768:] != 0).sum() > 100  # states keep moving after the wrap
     bad = np.argwhere(tok != r["tokens"])
     assert bad.size == 0, f"first mismatch (frame, stream) {bad[0]}"
     assert np.array_equal(ls.cpu().numpy(), r["lm_state"])
     assert np.array_equal(bs.cpu().numpy(), r["boost_state"])
+    return x, tok
+
+
+def test_long_run_past_the_lds_stamp_period():
+    """One launch of 33068 frames: the LDS rows of explicit arcs and phrase
+    transitions carry a stamp that counts the rows assembled and repeats after
+    16384, so the run crosses points where they are cleared; every token and the
+    final states equal the oracle's.  Frames whose raw argmax is blank assemble
+    no row: the others alone must be more than the period."""
+    x, tok = _long_run(F.FUSION_BLANK_AM, 32768 + 300, 2, 91)
+    for s in range(x.shape[1]):
+        scored = np.flatnonzero(x[:, s].argmax(1) != 0)
+        assert scored.size > STAMPS + 1000
+        assert (tok[scored[STAMPS]:, s] != 0).sum() > 100  # states keep moving after the wrap
+
+
+def test_long_run_with_kept_rows_past_the_stamp_period():
+    """Blank competing with the fused keys: a hypothesis that emitted blank keeps its
+    rows, and their stamp, for the next frame; the clears fall among such frames."""
+    x, tok = _long_run(F.FUSION_BLANK_COMPETE, 40000, 2.5, 92)
+    for s in range(x.shape[1]):
+        rows = np.concatenate([[True], tok[:-1, s] != 0])  # frames that assemble their rows
+        at = np.flatnonzero(rows)
+        assert at.size > STAMPS + 1000
+        near = slice(at[STAMPS] - 50, at[STAMPS] + 50)
+        assert 20 < (~rows[near]).sum() < 80
+
+
+def test_long_beam_past_the_stamp_period():
+    """A beam assembles its rows at every frame: 16684 frames of 2 x 2 slots in one
+    launch equal the same frames in calls of 5000, whose stamps never repeat, bit for
+    bit (the chunked beam is checked against the oracle elsewhere)."""
+    rng = np.random.default_rng(93)
+    V, S, B, k, T = 90, 2, 2, 2, STAMPS + 300
+    glm = F.ngram_load_arrays(tiny_random_lm(rng, V, 4, n_sent=2000))
+    gtr = F.boost_build_phrases(V, 0, tiny_random_phrases(rng, V, n=30, max_len=4, alphabet=20, with_completion=True))
+    H = S * B
+    x = torch.from_numpy((rng.standard_normal((T, H, V)) * 2).astype(np.float32)).to(dev())
+    got = []
+    for chunk in (T, 5000):
+        ls = torch.full((H,), V, dtype=torch.int32, device=dev())
+        bs = torch.zeros((H,), dtype=torch.int32, device=dev())
+        sc = torch.from_numpy(np.tile(np.array([0.0, -np.inf]), S)).to(dev())
+        outs = [F.run(glm, gtr, x[t:t + chunk], S, B, k, 0.5, 0.5, 0, F.FUSION_BLANK_COMPETE, ls, bs, sc)
+                for t in range(0, T, chunk)]
+        torch.cuda.synchronize()
+        assert F.fusion_device_status() == 0
+        got.append([torch.cat([o[n] for o in outs]).cpu() for n in ("tokens", "parents")] +
+                   [ls.cpu(), bs.cpu(), sc.cpu()])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
 
 
 def test_c3_batched_greedy_prefix():

@@ -11,6 +11,7 @@ import pytest
 import torch
 
 import oracle
+from oracle import traffic as checker
 import paper_2609_14991_amd as F
 from workloads import tiny_random_lm, tiny_random_phrases
 
@@ -60,7 +61,8 @@ def test_blank_frames(V, n_lm, mode):
 @pytest.mark.parametrize("V", [130, 1001, 2048])
 def test_blank_frames_counted(V):
     """A run that counts its bytes goes through every frame: one that blank takes
-    leaves nothing of its phrase state to the frames of the next state."""
+    leaves nothing of its phrase state to the frames of the next state.  The count
+    equals the independent one over the states visited."""
     rng = np.random.default_rng(V)
     S, T = 6, 150
     lm = tiny_random_lm(rng, V, 3, n_sent=400)
@@ -80,6 +82,8 @@ def test_blank_frames_counted(V):
     tok = out["tokens"].cpu().numpy()
     assert np.array_equal(tok, r["tokens"]), np.argwhere(tok != r["tokens"])[:3]
     assert np.array_equal(bs.cpu().numpy(), r["boost_state"])
+    visits = checker.visited_states(oracle.OracleLM(lm), oracle.OracleTrie(V, 0, ph), V, 0, 1, r["tokens"])
+    assert count.tolist() == list(checker.algorithmic_bytes(lm, ph, visits, T, beam=False))
 
 
 @pytest.mark.parametrize("V,n_lm", [(3, 1), (130, 2), (1001, 1), (2048, 1), (8190, 1)])
