@@ -1,6 +1,7 @@
-// Fusion step kernels for gfx950 and the C ABI entry points fusion_step /
-// fusion_run: Eq. (1) of the paper (Sec. III-C) with greedy or top-k
-// selection and a frame-synchronous beam.
+// The fusion kernel for gfx950: Eq. (1) of the paper (Sec. III-C) with greedy or
+// top-k selection and a frame-synchronous beam.  Its launches and the C ABI entry
+// points are in fusion_kernels.hip; each compiled shape is a file of its own
+// (fusion_w*.hip).
 //
 // Work mapping.  One workgroup per hypothesis (W = 64, 256 or 1024 lanes),
 // so a 64 x 4 beam keeps all 256 CUs busy.  Lane g owns the tokens
@@ -22,8 +23,8 @@
 //   4  key = (x + lambda*lm) + beta*boost per owned token, top-k per lane, per
 //      wave (shuffles) and per hypothesis; each candidate carries where its
 //      next LM / phrase state comes from, so no further lookup is needed;
-//   5  beam: the B workgroups of a stream publish their candidates, meet at a
-//      per-stream counter, and each ranks all B*k candidates (fp64 running
+//   5  beam: the B workgroups of a stream publish their candidates as tagged
+//      records, poll for all of the stream's, and each ranks the B*k (fp64 running
 //      score) to take its own new hypothesis.
 // No MFMA: ~10 flops per score over gathered data.
 #pragma once
@@ -276,8 +277,9 @@ __device__ __forceinline__ void merge_equal(double (&t)[Q], unsigned long long h
     int sl[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      // (after the hash's 48 bits are used up, the slot is the candidate's rank among
-      // all: mixed hashes never come to that)
+      // (once the hash's upper bits are used up, bits of a multiple of it.  The search ends
+      // whatever the bits: in each round the least open candidate of every slot finds
+      // itself there)
       sl[q] = (int)((shift < 45 ? hq[q] >> shift : hq[q] * 0x9E3779B97F4A7C15ull >> (shift % 50)) & (kHashSlots - 1));
       if (todo[q]) atomicMin(&tab[sl[q]], q * 64 + lane);
     }
@@ -755,8 +757,9 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   // row statistics of the logits of strip sw (the 64-lane strip of wave sw) held
   // in xs: strip max, sum of exp below it, lowest id holding the max (only the
   // acoustic blank decision needs it).  They depend on the logits alone, so those
-  // of frame t+1 are computed in frame t by the waves that are otherwise idle
-  // while wave 0 ends the frame (wave 1 takes wave 0's strip); frame 0's here
+  // of frame t+1 are computed in frame t by the waves other than wave 0 (wave 1
+  // takes wave 0's strip): in a beam they are idle while wave 0 ends the frame, and
+  // a greedy launch that needs the statistics keeps to the same split.  Frame 0's here
   auto row_stats = [&](const float (&xs)[NC][4], int sw, int V) {
     float xv[NC][4];  // tokens >= V: -inf
     float lmx = -INFINITY;
@@ -979,147 +982,147 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       }
     }
     if (!keep) {
-    if (STEP) {
-      // (a state below V + 2 is its own c_1; the first LM's context row takes the place
-      // of the dense row)
+      if (STEP) {
+        // (a state below V + 2 is its own c_1; the first LM's context row takes the place
+        // of the dense row)
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+          if (rp[i]) c1[i] = rec[i][0] & 0xFFFF;
+          if (ok && !(CTX && i == 0 && Dc >= 2)) load_row(lms[i].dense + (int64_t)c1[i] * V, lmval + i * Vp, V);
+        }
+      }
+      if (CTX && ok && Dc >= 2) load_row(lms[0].ctx_lm + (int64_t)crow * V, lmval + NL * Vp, V);
+      // ---- hop 2: first arcs of levels 2..m (flattened) and first phrase transitions --
+      int2 ab[NL][kUA];
+      int at[NL][kUA], tn[NL][kUA];  // at = level << 16 | offset within the level
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
-        if (rp[i]) c1[i] = rec[i][0] & 0xFFFF;
-        if (ok && !(CTX && i == 0 && Dc >= 2)) load_row(lms[i].dense + (int64_t)c1[i] * V, lmval + i * Vp, V);
-      }
-    }
-    if (CTX && ok && Dc >= 2) load_row(lms[0].ctx_lm + (int64_t)crow * V, lmval + NL * Vp, V);
-    // ---- hop 2: first arcs of levels 2..m (flattened) and first phrase transitions --
-    int2 ab[NL][kUA];
-    int at[NL][kUA], tn[NL][kUA];  // at = level << 16 | offset within the level
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
+        for (int u = 0; u < kUA; ++u) {
+          int f = u * W + g;
+          ab[i][u] = make_int2(INT_MAX, 0);
+          at[i][u] = 0;
+          tn[i][u] = 0;
+          // the level of flattened arc f against the (uniform) starts of the levels:
+          // the last level that starts at or before f; then f's offset within it
+          int L = 2, bL = lbeg[i][2], fo = f, e = 0;
 #pragma unroll
-      for (int u = 0; u < kUA; ++u) {
-        int f = u * W + g;
-        ab[i][u] = make_int2(INT_MAX, 0);
-        at[i][u] = 0;
-        tn[i][u] = 0;
-        // the level of flattened arc f against the (uniform) starts of the levels:
-        // the last level that starts at or before f; then f's offset within it
-        int L = 2, bL = lbeg[i][2], fo = f, e = 0;
-#pragma unroll
-        for (int L2 = 3; L2 < kMaxLevels; ++L2) {
-          e += lcnt[i][L2 - 1];  // first flattened index of level L2
-          const bool past = f >= e && L2 <= m[i];
-          L = past ? L2 : L;
-          bL = past ? lbeg[i][L2] : bL;
-          fo = past ? f - e : fo;
-        }
-        f = fo;
-        if (u * W + g < total_arcs[i]) {
-          at[i][u] = (L << 16) | f;
-          ab[i][u] = lms[i].arcs[bL + f];
-          if (L == Nl[i] - 1 && f < kAux) tn[i][u] = lms[i].top_next[bL + f - lms[i].arc_base[Nl[i] - 1]];
+          for (int L2 = 3; L2 < kMaxLevels; ++L2) {
+            e += lcnt[i][L2 - 1];  // first flattened index of level L2
+            const bool past = f >= e && L2 <= m[i];
+            L = past ? L2 : L;
+            bL = past ? lbeg[i][L2] : bL;
+            fo = past ? f - e : fo;
+          }
+          f = fo;
+          if (u * W + g < total_arcs[i]) {
+            at[i][u] = (L << 16) | f;
+            ab[i][u] = lms[i].arcs[bL + f];
+            if (L == Nl[i] - 1 && f < kAux) tn[i][u] = lms[i].top_next[bL + f - lms[i].arc_base[Nl[i] - 1]];
+          }
         }
       }
-    }
-    int4 dd[kUD];
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) {
-      const int j = u * W + g;
-      dd[u] = make_int4(INT_MAX, 0, 0, 0);
-      if (j < dcnt) dd[u] = tr.delta[dbeg + j];
-    }
-    if (ok && g == 0) {
-      if (!GR) hs.cur_q = qid;
-#pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        if (!GR) {
-          hs.cur_lm[i] = sid[i];
-          hs.c1[i] = c1[i];
-        }
-#pragma unroll
-        for (int L = 2; L < kMaxLevels; ++L) s_lbeg[i][L] = lbeg[i][L];
-      }
-    }
-    // ---- scatter (no ordering between levels: see arcw) ----------------------------
-    // an arc of level L is stored summed with the backoffs of levels L+1.., the
-    // addition order of the backoff recursion
-    auto put_arc = [&](int i, int L, int j, int2 a, int tnext) {
-      const int y = a.x;
-      if (y < V) {
-        float v = as_float(a.y);
-#pragma unroll
-        for (int L2 = 3; L2 < kMaxLevels; ++L2) {
-          if (L2 > m[i]) break;  // uniform: the levels above m back off by nothing
-          v = v + (L2 > L ? bo[i][L2] : 0.0f);
-        }
-        const uint32_t tag = (stamp << 16) | (uint32_t)((L << 13) | j);
-        __hip_atomic_fetch_max(arcw + i * Vp + y, ((unsigned long long)tag << 32) | (unsigned long long)__float_as_uint(v),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (L == Nl[i] - 1 && j < kAux) sTN[i * kAux + j] = tnext;
-      }
-    };
-    if (STEP) {
-      // the rows are cleared and the waves' statistics are there
-      lds_barrier();
-      if (wave == NW - 1) combine_stats();
-    }
-    if (ok) {
+      int4 dd[kUD];
 #pragma unroll
       for (int u = 0; u < kUD; ++u) {
         const int j = u * W + g;
-        if (j < dcnt) {
-          ptag[dd[u].x] = (stamp << 16) | (uint32_t)(j + 1);
-          if (ER) erow[dd[u].x] = as_float(dd[u].z);
+        dd[u] = make_int4(INT_MAX, 0, 0, 0);
+        if (j < dcnt) dd[u] = tr.delta[dbeg + j];
+      }
+      if (ok && g == 0) {
+        if (!GR) hs.cur_q = qid;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+          if (!GR) {
+            hs.cur_lm[i] = sid[i];
+            hs.c1[i] = c1[i];
+          }
+#pragma unroll
+          for (int L = 2; L < kMaxLevels; ++L) s_lbeg[i][L] = lbeg[i][L];
+        }
+      }
+      // ---- scatter (no ordering between levels: see arcw) ----------------------------
+      // an arc of level L is stored summed with the backoffs of levels L+1.., the
+      // addition order of the backoff recursion
+      auto put_arc = [&](int i, int L, int j, int2 a, int tnext) {
+        const int y = a.x;
+        if (y < V) {
+          float v = as_float(a.y);
+#pragma unroll
+          for (int L2 = 3; L2 < kMaxLevels; ++L2) {
+            if (L2 > m[i]) break;  // uniform: the levels above m back off by nothing
+            v = v + (L2 > L ? bo[i][L2] : 0.0f);
+          }
+          const uint32_t tag = (stamp << 16) | (uint32_t)((L << 13) | j);
+          __hip_atomic_fetch_max(arcw + i * Vp + y, ((unsigned long long)tag << 32) | (unsigned long long)__float_as_uint(v),
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (L == Nl[i] - 1 && j < kAux) sTN[i * kAux + j] = tnext;
+        }
+      };
+      if (STEP) {
+        // the rows are cleared and the waves' statistics are there
+        lds_barrier();
+        if (wave == NW - 1) combine_stats();
+      }
+      if (ok) {
+#pragma unroll
+        for (int u = 0; u < kUD; ++u) {
+          const int j = u * W + g;
+          if (j < dcnt) {
+            ptag[dd[u].x] = (stamp << 16) | (uint32_t)(j + 1);
+            if (ER) erow[dd[u].x] = as_float(dd[u].z);
+            if (j < kAux) {
+              sE[j + 1] = as_float(dd[u].z);
+              sDT[j] = dd[u].y;
+            }
+          }
+        }
+        for (int j = kUD * W + g; j < dcnt; j += W) {
+          const int4 e = tr.delta[dbeg + j];
+          ptag[e.x] = (stamp << 16) | (uint32_t)(j + 1);
+          if (ER) erow[e.x] = as_float(e.z);
           if (j < kAux) {
-            sE[j + 1] = as_float(dd[u].z);
-            sDT[j] = dd[u].y;
+            sE[j + 1] = as_float(e.z);
+            sDT[j] = e.y;
           }
         }
-      }
-      for (int j = kUD * W + g; j < dcnt; j += W) {
-        const int4 e = tr.delta[dbeg + j];
-        ptag[e.x] = (stamp << 16) | (uint32_t)(j + 1);
-        if (ER) erow[e.x] = as_float(e.z);
-        if (j < kAux) {
-          sE[j + 1] = as_float(e.z);
-          sDT[j] = e.y;
-        }
-      }
 #pragma unroll
-      for (int i = 0; i < NL; ++i)
+        for (int i = 0; i < NL; ++i)
 #pragma unroll
-        for (int u = 0; u < kUA; ++u)
-          if (at[i][u] != 0) put_arc(i, at[i][u] >> 16, at[i][u] & 0xFFFF, ab[i][u], tn[i][u]);
-      // arcs beyond the first kUA * W of the flattened levels
+          for (int u = 0; u < kUA; ++u)
+            if (at[i][u] != 0) put_arc(i, at[i][u] >> 16, at[i][u] & 0xFFFF, ab[i][u], tn[i][u]);
+        // arcs beyond the first kUA * W of the flattened levels
 #pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int N = Nl[i];
-        int covered = kUA * W;
+        for (int i = 0; i < NL; ++i) {
+          const int N = Nl[i];
+          int covered = kUA * W;
 #pragma unroll
-        for (int L = 2; L < kMaxLevels; ++L) {
-          if (L > m[i]) break;  // uniform
-          const int bL = lbeg[i][L], cL = lcnt[i][L];
-          const int done = min(cL, max(0, covered));
-          covered -= cL;
-          const int2 *A = lms[i].arcs + bL;
-          for (int j0 = done; j0 < cL; j0 += 4 * W) {
-            int2 a4[4];
-            int t4[4];
+          for (int L = 2; L < kMaxLevels; ++L) {
+            if (L > m[i]) break;  // uniform
+            const int bL = lbeg[i][L], cL = lcnt[i][L];
+            const int done = min(cL, max(0, covered));
+            covered -= cL;
+            const int2 *A = lms[i].arcs + bL;
+            for (int j0 = done; j0 < cL; j0 += 4 * W) {
+              int2 a4[4];
+              int t4[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int j = j0 + u * W + g;
-              a4[u] = j < cL ? A[j] : make_int2(INT_MAX, 0);
-              t4[u] = (L == N - 1 && j < cL && j < kAux) ? lms[i].top_next[bL + j - lms[i].arc_base[N - 1]] : 0;
-            }
+              for (int u = 0; u < 4; ++u) {
+                const int j = j0 + u * W + g;
+                a4[u] = j < cL ? A[j] : make_int2(INT_MAX, 0);
+                t4[u] = (L == N - 1 && j < cL && j < kAux) ? lms[i].top_next[bL + j - lms[i].arc_base[N - 1]] : 0;
+              }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int j = j0 + u * W + g;
-              if (j < cL) put_arc(i, L, j, a4[u], t4[u]);
+              for (int u = 0; u < 4; ++u) {
+                const int j = j0 + u * W + g;
+                if (j < cL) put_arc(i, L, j, a4[u], t4[u]);
+              }
             }
           }
         }
       }
-    }
-    __builtin_amdgcn_s_waitcnt(0);  // the dense rows have landed in LDS
-    __syncthreads();
+      __builtin_amdgcn_s_waitcnt(0);  // the dense rows have landed in LDS
+      __syncthreads();
     }
     // ---- the row statistics of this frame ---------------------------------------------
     // the log-sum-exp is needed by wave 0 (selected scores, beam totals) and, for
@@ -1680,7 +1683,8 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
         }
       } else if constexpr (BEAM) {
         // ---- beam: publish this hypothesis' candidates, meet the stream, rank all ----
-        // A candidate record is XW = 4 + NL 64-bit words, each carrying the frame
+        // A candidate record is XW = 3 + NL 64-bit words (one more when recombining),
+        // each carrying the frame
         // tag in its top 16 bits over 48 bits of payload: the total score S_b +
         // fused (fp64), the first LM's and the phrase source, the token, the
         // parent's c_1 (first LM) and flags, for a second LM its source and the

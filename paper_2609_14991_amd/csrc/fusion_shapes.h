@@ -21,7 +21,7 @@ struct Params {
   float *scores;  // fusion_step outputs [H, k]; a one-frame greedy call has no scores (NULL) and
   int32_t *next_lm;     // its states in place (next_boost NULL without a phrase tree)
   int32_t *next_boost;
-  unsigned long long *xchg;  // beam exchange [S][2][B][k] candidate records of four tagged words
+  unsigned long long *xchg;  // beam exchange [S][2][B][k] candidate records of 3 + n_lm (+ 1 recombining) tagged words
   unsigned long long *hist;  // recombination: [H] in/out history hashes (0: derive from the initial states) or NULL
   unsigned *tickets;         // beam: arrival counters, one per blockIdx class (8 with xcd_map, else 1)
   // t_base: the number of frames decoded by earlier calls of a frame loop that
