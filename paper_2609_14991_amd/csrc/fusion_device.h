@@ -570,7 +570,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   // rows may be shorter than a strip, reads single tokens
   constexpr bool SHIFT = !AL && W > 64;
   float xraw[NC][4];
-  float xraw0[NC][4];  // wave 1: wave 0's strip too, for its row statistics
+  float xraw0[NC][4];  // a beam's wave 1: wave 0's strip too, for its row statistics
   auto fetch_strip = [&](const rsrc_t &xr, float (&dst)[NC][4], int off) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -699,7 +699,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   auto fetch_logits = [&]() {
     const rsrc_t xr = row_rsrc(xrow, p.V);
     fetch_strip(xr, xraw, voff);
-    if (NW > 1 && !STEP && wave == 1) fetch_strip(xr, xraw0, lane * 16);
+    if (NW > 1 && BEAM && wave == 1) fetch_strip(xr, xraw0, lane * 16);
   };
   float rE[NC][4];
 #pragma unroll
@@ -756,10 +756,10 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
   }
   // row statistics of the logits of strip sw (the 64-lane strip of wave sw) held
   // in xs: strip max, sum of exp below it, lowest id holding the max (only the
-  // acoustic blank decision needs it).  They depend on the logits alone, so those
-  // of frame t+1 are computed in frame t by the waves other than wave 0 (wave 1
-  // takes wave 0's strip): in a beam they are idle while wave 0 ends the frame, and
-  // a greedy launch that needs the statistics keeps to the same split.  Frame 0's here
+  // acoustic blank decision needs it).  They depend on the logits alone, so a beam
+  // computes those of frame t+1 in frame t in the waves that are idle while wave 0
+  // ends the frame (wave 1 takes wave 0's strip), frame 0's here; a step and a greedy
+  // frame compute theirs in the shadow of the record's load
   auto row_stats = [&](const float (&xs)[NC][4], int sw, int V) {
     float xv[NC][4];  // tokens >= V: -inf
     float lmx = -INFINITY;
@@ -830,7 +830,16 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       __builtin_amdgcn_global_load_lds(drow + (y0 < V ? y0 : 0), (lds_ptr_t)(row + wbase * 4), 16, 0, 0);
     }
   };
-  if (!STEP && stats) {
+  // (the last of the n waves to come here combines)
+  auto combine_last = [&](int n) {
+    int done = 0;
+    if (lane == 0) done = __hip_atomic_fetch_add(&s_nstat, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (uni(done) == n - 1) {
+      combine_stats();
+      if (lane == 0) s_nstat = 0;
+    }
+  };
+  if (BEAM || (GR && NW == 1 && stats)) {
     row_stats(xraw, wave, p.V);
     __syncthreads();
     if (wave == NW - 1) combine_stats();
@@ -941,6 +950,13 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       row_stats(xraw, wave, V);
       take_strip();
       __builtin_amdgcn_sched_barrier(0);  // the record is waited for after this, not before
+    } else if (GR && NW > 1 && stats) {
+      // a greedy frame's own, under the latency of its records.  (As work that the
+      // waves did after the last frame's selection they delayed the next frame: 64 streams
+      // of 100 frames with their fused rows, blank competing, 4096 tokens: 478 us,
+      // 415 so; 1024: 394, 359; 8190: 671, 620; mode A at 4096: 492, 435)
+      row_stats(xraw, wave, V);
+      combine_last(NW);
     } else if (NW == 1 && t > 0 && stats) {  // a single wave has no idle helper
       row_stats(xraw, 0, V);
       combine_stats();
@@ -1124,6 +1140,7 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       __builtin_amdgcn_s_waitcnt(0);  // the dense rows have landed in LDS
       __syncthreads();
     }
+    if (GR && NW > 1 && keep && stats) lds_barrier();  // (else the rows' barrier)
     // ---- the row statistics of this frame ---------------------------------------------
     // the log-sum-exp is needed by wave 0 (selected scores, beam totals) and, for
     // fused rows, by every wave; the acoustic argmax (mode A) by every wave
@@ -1468,17 +1485,12 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
       s_steps += 1ull;
     }
     lds_barrier();
-    // the next frame's row statistics, by the waves other than wave 0; the last of
-    // them to finish combines them (ahead of the frame's end, off wave 0's path)
-    if (!STEP && NW > 1 && wave != 0 && stats && tn < p.T) {
+    // a beam's next frame's row statistics, by the waves other than wave 0 (ahead of the
+    // frame's end, off wave 0's path)
+    if (BEAM && NW > 1 && wave != 0 && tn < p.T) {
       row_stats(xraw, wave, V);
       if (wave == 1) row_stats(xraw0, 0, V);
-      int done = 0;
-      if (lane == 0) done = __hip_atomic_fetch_add(&s_nstat, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (uni(done) == NW - 2) {
-        combine_stats();
-        if (lane == 0) s_nstat = 0;
-      }
+      combine_last(NW - 1);
     }
     if constexpr (GR) {
       // ---- greedy: the best of the waves' bests, in every wave ------------------------
@@ -1529,7 +1541,6 @@ __global__ void __launch_bounds__(W, W == 64 ? 1 : 4) fusion_kernel(Params p) {
         hs.qsrc = st_q;
         hs.y = cy;
       }
-      if (stats) lds_barrier();  // the next frame's statistics
       continue;
     }
     // ---- the hypothesis' top-k (wave 0): the K-entry lists of the NW waves spread
